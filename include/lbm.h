@@ -196,12 +196,16 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init,
 
 /* Advance n >= 0 steps.  g_scale: NULL (s(t) = 1) or n host doubles, the factor s(t)
  * of g(x) for each step.  Enqueues work only (no synchronisation), except as below.
+ * D2Q9: up to five steps are taken by one launch (tiles that recompute their margins), except
+ * with debug_poison or where a periodic lattice has fewer than three rows; the launch
+ * configuration (lbm_tuning) is that of the single steps that remain.
  * Small lattices (N <= 2^21 nodes), where launch overhead dominates: when n covers at
- * least two chunks of 64 steps and neither monitor_every nor debug_poison is set, the
- * chunks are replayed from a HIP graph captured once per buffer parity (the factors s(t)
+ * least two chunks of 64 steps (70 with five steps a launch, 66 with three) and neither
+ * monitor_every nor debug_poison is set, the chunks are replayed from a HIP graph captured
+ * once per buffer parity (the factors s(t)
  * are then staged in pinned host memory, uploaded asynchronously and read on the device;
  * the call waits only for the previous call's upload to have completed); the remainder
- * runs as single launches.  The results are identical to single launches.
+ * runs as direct launches.  The results are identical to single launches of one step.
  * Monitors in the step: if monitor_every is K > 0, after every step whose time t is a
  * multiple of K the monitor record of time t is computed on the device (with the
  * residual against time t - 1, whose velocity is recorded one step earlier; K = 1

@@ -8,7 +8,8 @@
  * collision model and storage mode, and all are advanced by ONE persistent kernel
  * launch per time step: a fixed grid of workgroups walks a flattened table of
  * equal-sized tiles (one tile = one workgroup's worth of nodes of one domain), so
- * uneven domains load-balance.  lbm_batch_run captures K steps plus the convergence
+ * uneven domains load-balance.  On D2Q9 a launch takes up to five steps where every periodic
+ * domain has at least three rows (one workgroup a tile, margins recomputed).  lbm_batch_run captures K steps plus the convergence
  * monitors as one HIP graph and replays it; per-domain convergence is decided on the
  * device, and the tiles of converged domains are skipped.
  *

@@ -37,6 +37,11 @@ struct BatchTile {
   int dom, x0, y0, z;
 };
 
+// A tile of a launch of several steps (lbm_multistep.h): its first owned node and owned size.
+struct BatchMultiTile {
+  int dom, x0, y0, ox, oy;
+};
+
 // This lane's node of a tile; false if it lies beyond the domain.
 __device__ __forceinline__ bool tile_xy(const BatchTile &t, const BatchDom &dm, int &x, int &y) {
   if (dm.tbx_log2 < 0) {

@@ -2,6 +2,7 @@
 // domains, the tile table, graph capture and replay, per-domain transfers, the tuner.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <limits>
@@ -80,7 +81,11 @@ struct lbm_batch {
   size_t scratch_bytes = 0;
   size_t bytes = 0;
   lbm_batch_tuning tune{0, 8, 1};
-  int ncu = 256;
+  int ncu = 256, lds_cu = 0;
+  // several steps a launch (D2Q9): steps (0: none), tiles and their LDS
+  int multi_K = 0, nmulti = 0;
+  unsigned multi_lds = 0;
+  void *multi_d = nullptr;
   // captured graph of one check interval
   hipGraphExec_t exec = nullptr;
   hipGraph_t graph = nullptr;
@@ -167,6 +172,9 @@ struct lbm_batch {
     b.state = state_d;
     b.window = 1;  // set by the monitor passes of a check interval
     b.partials = partials;
+    b.multi = multi_d;
+    b.nmulti = nmulti;
+    b.multi_lds = multi_lds;
     return b;
   }
 };
@@ -268,7 +276,7 @@ void release(lbm_batch *b) {
   if (b->cap) (void)hipStreamDestroy(b->cap);
   void *ptrs[] = {b->buf[0], b->buf[1], b->gbuf,     b->urec,         b->uchk,  b->doms_d,
                   b->tiles_d, b->tile_begin_d, b->tile_end_d, b->partials, b->active_d,
-                  b->n_active_d, b->state_d, b->scratch};
+                  b->n_active_d, b->state_d, b->scratch, b->multi_d};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   b->magic = 0;
@@ -298,21 +306,83 @@ int reset_states(lbm_batch *b) {
   return LBM_OK;
 }
 
+// The tiles of launches of several steps, where every domain allows them: the steps of the
+// domain with the fewest, columns as multi_columns, and the rows a tile owns at most chosen
+// for the batch as a whole (multi_cost), spread evenly over a domain.
+int build_multi(lbm_batch *b) {
+  if (!b->ops->batch_multi) return LBM_OK;
+  const size_t sb = storage_bytes(b->storage);
+  int K = lbm::MULTI_STEPS;
+  for (const auto &m : b->dom) {
+    K = std::min(K, lbm::multi_steps(m.ny, m.wall[1]));
+    if ((uint64_t)m.ps * sb >= (1ull << 32)) K = 0;
+  }
+  if (!K) return LBM_OK;
+  int rows = 0;
+  double best = 0;
+  for (int oy = 1; oy <= lbm::MULTI_ROWS && lbm::multi_lds(oy, K, sb) <= (size_t)b->lds_cu; ++oy) {
+    int64_t n = 0;
+    for (const auto &m : b->dom)
+      n += (int64_t)lbm::multi_columns(m.nx, K) * ((m.ny + oy - 1) / oy);
+    const double cost = lbm::multi_cost(n, oy, K, b->ncu);
+    if (rows && cost >= best) continue;
+    best = cost;
+    rows = oy;
+  }
+  if (!rows) return LBM_OK;
+  std::vector<lbm::BatchMultiTile> tiles;
+  int tallest = 0;
+  for (int d = 0; d < b->ndom; ++d) {
+    const lbm::BatchDom &m = b->dom[d];
+    const int ntx = lbm::multi_columns(m.nx, K), nty = (m.ny + rows - 1) / rows;
+    const int ox = (m.nx + ntx - 1) / ntx, oy = (m.ny + nty - 1) / nty;
+    tallest = std::max(tallest, oy);
+    for (int y0 = 0; y0 < m.ny; y0 += oy)
+      for (int x0 = 0; x0 < m.nx; x0 += ox)
+        tiles.push_back({d, x0, y0, std::min(ox, m.nx - x0), std::min(oy, m.ny - y0)});
+  }
+  int rc = b->dalloc(&b->multi_d, tiles.size() * sizeof(tiles[0]));
+  if (rc) return rc;
+  HIP_TRY(hipMemcpyAsync(b->multi_d, tiles.data(), tiles.size() * sizeof(tiles[0]),
+                         hipMemcpyHostToDevice, b->stream));
+  HIP_TRY(hipStreamSynchronize(b->stream));  // tiles is released on return
+  b->multi_K = K;
+  b->nmulti = (int)tiles.size();
+  b->multi_lds = (unsigned)lbm::multi_lds(tallest, K, sb);
+  return LBM_OK;
+}
+
+// Enqueue n steps on stream s from buffer `from`, which becomes the one they end in: several
+// a launch where the batch has such tiles.  Each launch takes an odd number of steps, so the
+// buffers alternate as they do step by step.
+int enqueue_steps(lbm_batch *b, int64_t n, int &from, hipStream_t s) {
+  while (n > 0) {
+    int k = (int)std::min<int64_t>(b->multi_K, n);
+    if (k % 2 == 0) --k;
+    if (k >= 3) {
+      HIP_TRY(b->ops->batch_multi(b->launch(from), k, s));
+    } else {
+      k = 1;
+      HIP_TRY(b->ops->batch_step(b->launch(from), s));
+    }
+    from ^= 1;
+    n -= k;
+  }
+  return LBM_OK;
+}
+
 // Enqueue one check interval on stream s: K-1 steps, record u, one step, compare +
 // record, decide.
 int enqueue_interval(lbm_batch *b, int K, double tol, int stall, hipStream_t s) {
   int from = b->cur;
-  for (int k = 0; k < K; ++k) {
-    if (k == K - 1) {
-      lbm::BatchLaunch m = b->launch(from);
-      m.mode = 2;
-      m.window = stall;
-      HIP_TRY(b->ops->batch_monitor(m, s));
-    }
-    HIP_TRY(b->ops->batch_step(b->launch(from), s));
-    from ^= 1;
-  }
+  int rc = enqueue_steps(b, K - 1, from, s);
+  if (rc) return rc;
   lbm::BatchLaunch m = b->launch(from);
+  m.mode = 2;
+  m.window = stall;
+  HIP_TRY(b->ops->batch_monitor(m, s));
+  if ((rc = enqueue_steps(b, 1, from, s))) return rc;
+  m = b->launch(from);
   m.mode = 4;
   m.window = stall;
   HIP_TRY(b->ops->batch_monitor(m, s));
@@ -357,6 +427,9 @@ int lbm_batch_init(const lbm_domain *domains, int32_t ndom, int32_t lattice, int
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
     b->ncu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
+  if (hipDeviceGetAttribute(&b->lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
+      hipSuccess)
+    b->lds_cu = 0;
 
   // pack the domains
   const size_t ab = arith_bytes(storage);
@@ -452,6 +525,7 @@ int lbm_batch_init(const lbm_domain *domains, int32_t ndom, int32_t lattice, int
       hipSuccess)
     return bail(set_error(LBM_EDEVICE, "uploading force tables failed"));
   if ((rc = build_tiles(b))) return bail(rc);
+  if ((rc = build_multi(b))) return bail(rc);
   if ((rc = reset_states(b))) return bail(rc);
   // initial states, one domain at a time
   for (int d = 0; d < ndom; ++d) {
@@ -494,10 +568,8 @@ int lbm_batch_init(const lbm_domain *domains, int32_t ndom, int32_t lattice, int
 int lbm_batch_advance(lbm_batch *b, int64_t n) {
   if (!valid(b)) return set_error(LBM_ESTATE, "invalid batch");
   if (n < 0) return set_error(LBM_EINVAL, "negative step count");
-  for (int64_t s = 0; s < n; ++s) {
-    HIP_TRY(b->ops->batch_step(b->launch(b->cur), b->stream));
-    b->cur ^= 1;
-  }
+  const int rc = enqueue_steps(b, n, b->cur, b->stream);
+  if (rc) return rc;
   if (n) HIP_TRY(lbm::add_domain_steps(b->active_d, b->state_d, b->ndom, n, b->stream));
   return LBM_OK;
 }

@@ -1,4 +1,6 @@
 // Kernels of the D3Q27 lattice (see lbm_lattice_impl.h).
 #define LBM_LAT D3Q27
 #define LBM_OPS ops_d3q27
+#define LBM_MULTI nullptr
+#define LBM_BATCH_MULTI nullptr
 #include "lbm_lattice_impl.h"

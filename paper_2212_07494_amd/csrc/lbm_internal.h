@@ -63,6 +63,44 @@ struct LaunchDesc {
   int gs_j;
 };
 
+// Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
+// tile, steps of a launch, threads of a workgroup, and the most rows a plan lets a tile own.
+constexpr int MULTI_W = 64;
+constexpr int MULTI_STEPS = 5;
+constexpr int MULTI_THREADS = 512;
+constexpr int MULTI_ROWS = 27;
+
+// Launch of several steps in one pass over a two-dimensional lattice (lbm_multistep.h): K
+// steps (odd, at least 3; 0: no such plan), tiles of ox x oy nodes in an ntx x nty grid,
+// workgroups with `lds` bytes of LDS.
+struct MultiPlan {
+  int K, ox, oy, ntx, nty;
+  unsigned lds;
+};
+
+// The tiles a lattice's nx columns are split into, one beside the other, for K steps a
+// launch: one of up to 64 columns that wraps (or bounces) inside itself, else tiles that
+// leave room for K - 1 columns more on each side.
+inline int multi_columns(int nx, int K) {
+  const int room = nx <= MULTI_W ? nx : MULTI_W - 2 * (K - 1);
+  return (nx + room - 1) / room;
+}
+// LDS of a tile of oy rows, and the steps of a launch on a lattice of ny rows (0: none; a
+// periodic lattice wraps once, and one of few rows would mostly compute its margins).
+inline size_t multi_lds(int oy, int K, size_t elem) {
+  return (size_t)(oy + 2 * (K - 1)) * MULTI_W * 9 * elem;
+}
+inline int multi_steps(int ny, bool wy) { return wy || ny >= 12 ? MULTI_STEPS : (ny >= 3 ? 3 : 0); }
+// Relative time of a launch of `tiles` tiles of oy rows: the compute units take them in
+// turn, and a tile costs the rows of its K stages and about five more for its start and end.
+// The fastest heights sit where the tiles just fill the compute units once, twice, ...:
+// 512^2 FP32-shifted (10 columns) 22 rows, 240 tiles, 2.95 us a step against 4.08 at 20 rows,
+// 260 tiles; 900^2 (17 columns) 20 rows, 765 tiles, 6.1 against 7.1 at 18 rows.  MULTI_ROWS
+// keeps two workgroups a compute unit in FP32 (28 rows at 2048^2: 36 us a step, 26: 26).
+inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
+  return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
+}
+
 // One launch of the batched engine's persistent kernels.
 struct BatchLaunch {
   int coll, storage, variant;
@@ -81,6 +119,10 @@ struct BatchLaunch {
   int window;         // monitor: checks per coherence window
   int mode;           // monitor: 2 record, 4 compare + record
   double *partials;   // monitor: BATCH_PARTIALS per tile
+  // several steps a launch: the tiles (device BatchMultiTile[nmulti]) and their LDS
+  const void *multi;
+  int nmulti;
+  unsigned multi_lds;
 };
 
 // Per-tile slots of the batched monitor: sum |u(t) - u(t-1)|^2, sum |u|^2, non-finite
@@ -92,6 +134,9 @@ struct LatticeOps {
   const int *E;     // host: the Q velocities, Q x 3 (x, y, z)
   const double *W;  // host: the Q weights
   hipError_t (*step)(const LaunchDesc &, hipStream_t);
+  // k <= plan.K steps (k odd, at least 3) in one launch, with the force factors gs[0..k) or
+  // (NULL) the descriptor's; NULL for lattices without such kernels
+  hipError_t (*multi)(const LaunchDesc &, const MultiPlan &, int k, const double *gs, hipStream_t);
   // pi: optional non-equilibrium second moment, 6 binary64 planes (xx, yy, zz, xy, xz, yz)
   hipError_t (*init)(const LaunchDesc &, const double *rho, const double *u, double rho0,
                      const double *pi, hipStream_t);
@@ -111,6 +156,8 @@ struct LatticeOps {
                         double *partials, hipStream_t);
   hipError_t (*batch_step)(const BatchLaunch &, hipStream_t);
   hipError_t (*batch_monitor)(const BatchLaunch &, hipStream_t);
+  // k steps (odd, at least 3) of every active domain in one launch; NULL as for multi
+  hipError_t (*batch_multi)(const BatchLaunch &, int k, hipStream_t);
 };
 
 // Per-domain convergence state of the batched engine (device array, one per domain).
@@ -128,6 +175,12 @@ hipError_t decide_domains(const int *tile_begin, const int *tile_end, const doub
                           void *state, int *active, int *n_active, int ndom, double tol,
                           int stall_checks, int steps, hipStream_t s);
 hipError_t add_domain_steps(const int *active, void *state, int ndom, int64_t n, hipStream_t s);
+
+// lbm_d2q9_multi.hip
+MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu);
+hipError_t multi_step_d2q9(const LaunchDesc &, const MultiPlan &, int k, const double *gs,
+                           hipStream_t);
+hipError_t batch_multi_d2q9(const BatchLaunch &, int k, hipStream_t);
 
 const LatticeOps &ops_d2q9();
 const LatticeOps &ops_d3q19();

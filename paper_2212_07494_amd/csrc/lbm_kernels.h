@@ -204,25 +204,10 @@ struct StepArgs {
   int xcd;      // 1: XCD-contiguous block placement (xcd_block), 0: dispatch order
 };
 
-// One node of the fused step: pull the populations (periodic wrap or halfway
-// bounce-back), collide with the force, store at the node's own slots.
-template <class L, int COLL, class S, class T, int MEM>
-__device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restrict__ fout,
-                                          const Geom &geo, int x, int y, int z,
-                                          uint32_t sm, bool fast, const T (&g)[3], T shift,
-                                          T c0, T c1, T c2 = T(0), T c3 = T(0), T c4 = T(0)) {
-  T d[L::Q];
-  if (fast) {
-    static_for<L::Q>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      d[i] = load_v<MEM, S, T>(pull_ptr_periodic<L, i>(fin, x, y, z, geo));
-    });
-  } else {
-    static_for<L::Q>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      d[i] = load_v<MEM, S, T>(fin + pull_slot<L, i>(x, y, z, geo, sm));
-    });
-  }
+// The collision of code COLL (LaunchDesc::coll) with its coefficients.
+template <class L, int COLL, class T>
+__device__ __forceinline__ void collide_node(T (&d)[L::Q], T shift, const T (&g)[3], T c0, T c1,
+                                             T c2, T c3, T c4) {
   if constexpr (COLL == 0) {
     collide_bgk<L>(d, shift, g, BGKCoef<T>{c0, c1});
   } else {
@@ -242,6 +227,28 @@ __device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restri
     else
       collide_rmrt<L>(d, shift, g, RMRTCoef<T>{c0, c1, c2, c3});
   }
+}
+
+// One node of the fused step: pull the populations (periodic wrap or halfway
+// bounce-back), collide with the force, store at the node's own slots.
+template <class L, int COLL, class S, class T, int MEM>
+__device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restrict__ fout,
+                                          const Geom &geo, int x, int y, int z,
+                                          uint32_t sm, bool fast, const T (&g)[3], T shift,
+                                          T c0, T c1, T c2 = T(0), T c3 = T(0), T c4 = T(0)) {
+  T d[L::Q];
+  if (fast) {
+    static_for<L::Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      d[i] = load_v<MEM, S, T>(pull_ptr_periodic<L, i>(fin, x, y, z, geo));
+    });
+  } else {
+    static_for<L::Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      d[i] = load_v<MEM, S, T>(fin + pull_slot<L, i>(x, y, z, geo, sm));
+    });
+  }
+  collide_node<L, COLL>(d, shift, g, c0, c1, c2, c3, c4);
   if (fast) {
     const uint32_t o = (uint32_t)(y * geo.nx + x);
     static_for<L::Q>([&](auto I) {

@@ -1,6 +1,7 @@
 // Launchers of one lattice's kernels; included once per lattice unit with LBM_LAT set
 // to the lattice struct (D2Q9, D3Q19, D3Q27, D3Q39) and LBM_OPS to the exported table
-// name.  The batched engine is built for the lattices of at most 27 populations.
+// name.  LBM_MULTI and LBM_BATCH_MULTI name its multi-step
+// launchers (or are nullptr).  The batched engine is built for the lattices of at most 27 populations.
 #pragma once
 
 #include "lbm_batch_kernels.h"
@@ -242,6 +243,7 @@ const LatticeOps &LBM_OPS() {
                                  &LBM_LAT::E[0][0],
                                  &LBM_LAT::W[0],
                                  &impl::Ops<LBM_LAT>::step,
+                                 LBM_MULTI,
                                  &impl::Ops<LBM_LAT>::init,
                                  &impl::Ops<LBM_LAT>::gather,
                                  &impl::Ops<LBM_LAT>::solid_words,
@@ -249,7 +251,8 @@ const LatticeOps &LBM_OPS() {
                                  &impl::Ops<LBM_LAT>::waves,
                                  &impl::Ops<LBM_LAT>::moments,
                                  &impl::Ops<LBM_LAT>::batch_step,
-                                 &impl::Ops<LBM_LAT>::batch_monitor};
+                                 &impl::Ops<LBM_LAT>::batch_monitor,
+                                 LBM_BATCH_MULTI};
   return ops;
 }
 

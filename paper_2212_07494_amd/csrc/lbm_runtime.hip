@@ -94,6 +94,7 @@ unsigned lds_for_cap(int cap, int bx, int by, int lds_cu, int lds_block) {
   if (pad < lo) pad = hi;
   return (unsigned)pad;
 }
+
 constexpr uint64_t kFnvBasis = 0xcbf29ce484222325ull;
 size_t arith_bytes(int s) { return s == LBM_F64 ? 8 : 4; }
 bool shifted(int s) { return s == LBM_F32_SHIFTED || s == LBM_F16_SHIFTED; }
@@ -207,6 +208,7 @@ struct lbm_ctx {
   double last_scale = 1.0;
   double c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0, shift = 0;
   int bx = 64, by = 4, variant = 0;
+  lbm::MultiPlan multi{};         // K = 0: every step is a launch of its own
   int lds_cu = 0, lds_block = 0;  // LDS bytes of a CU and the most one workgroup may take
   lbm_monitors mon{};
 
@@ -706,6 +708,9 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
     c->lds_cu = 0;  // no occupancy caps
     c->lds_block = 0;
   }
+  int ncu = 0;
+  if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+    ncu = 0;
   c->p = *p;
   c->p.g_data = nullptr;
   if (p->allocator) c->alloc = *p->allocator;
@@ -734,6 +739,9 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
     }
   }
   block_shape(p->nx, c->bx, c->by);
+  if (c->ops->multi && !p->debug_poison)
+    c->multi = lbm::multi_plan(p->nx, p->ny, p->bc[1] == LBM_WALLS, storage_bytes(p->storage),
+                               c->lds_cu, ncu);
   const dim3 grid((p->nx + c->bx - 1) / c->bx, (p->ny + c->by - 1) / c->by, p->nz);
   c->nblocks = (int64_t)grid.x * grid.y * grid.z;
   c->nblocks_cap = c->nblocks;
@@ -850,14 +858,55 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
 
 namespace {
 
-constexpr int kGraphChunk = 64;             // steps per captured graph (even)
+constexpr int kGraphChunk = 64;             // steps per captured graph (even), about
 constexpr int64_t kGraphMaxNodes = 1 << 21;  // larger lattices are not launch-bound
+
+// Steps of one captured graph: an even number of launches of multi.K steps where the
+// lattice has such launches.
+int graph_chunk(const lbm_ctx *c) {
+  const int two = 2 * c->multi.K;
+  return two ? (kGraphChunk + two - 1) / two * two : kGraphChunk;
+}
 
 // Whether n steps of c run as graph replays: a small lattice, at least two chunks, no
 // in-step monitors or poison pass.
 bool graph_steps(const lbm_ctx *c, int64_t n) {
-  return c->N <= kGraphMaxNodes && n >= 2 * kGraphChunk && c->p.monitor_every == 0 &&
+  return c->N <= kGraphMaxNodes && n >= 2 * graph_chunk(c) && c->p.monitor_every == 0 &&
          !c->p.debug_poison;
+}
+
+// Steps of the next launch when n are left: the most that the plan covers, an odd number
+// (each launch moves the state to the other buffer, so the buffers alternate as they do
+// step by step), or 1.
+int next_steps(const lbm_ctx *c, int64_t n) {
+  int k = (int)std::min<int64_t>(c->multi.K, n);
+  if (k % 2 == 0) --k;
+  return k >= 3 ? k : 1;
+}
+
+// One launch of k steps (next_steps) of d on stream s; gs: their force factors or NULL.
+hipError_t launch_steps(const lbm_ctx *c, lbm::LaunchDesc &d, int k, const double *gs,
+                        hipStream_t s) {
+  if (k > 1) return c->ops->multi(d, c->multi, k, gs, s);
+  if (gs) d.gscale = gs[0];
+  return c->ops->step(d, s);
+}
+
+// n steps from the current state as single launches; gs: their force factors or NULL (1).
+int eager_steps(lbm_ctx *c, int64_t n, const double *gs) {
+  for (int64_t s = 0; s < n;) {
+    const int k = next_steps(c, n - s);
+    if (c->p.debug_poison)
+      HIP_TRY(lbm::fill_nan(c->buf[c->cur ^ 1], (size_t)c->Q * c->N * storage_bytes(c->p.storage),
+                            c->stream));
+    lbm::LaunchDesc d = c->desc(1.0);
+    HIP_TRY(launch_steps(c, d, k, gs ? gs + s : nullptr, c->stream));
+    c->cur ^= 1;
+    c->t += k;
+    s += k;
+    c->last_scale = gs ? gs[s - 1] : 1.0;
+  }
+  return LBM_OK;
 }
 
 // The graph of one chunk from the current buffer, with device force factors (scaled) or
@@ -876,7 +925,9 @@ int chunk_graph(lbm_ctx *c, bool scaled, hipGraphExec_t *out) {
   HIP_TRY(hipStreamBeginCapture(c->cap, hipStreamCaptureModeThreadLocal));
   hipError_t err = hipSuccess;
   int cur = c->cur;
-  for (int j = 0; j < kGraphChunk && err == hipSuccess; ++j) {
+  const int chunk = graph_chunk(c);
+  for (int j = 0, k; j < chunk && err == hipSuccess; j += k) {
+    k = next_steps(c, chunk - j);
     const int saved = c->cur;
     c->cur = cur;
     lbm::LaunchDesc d = c->desc(1.0);
@@ -886,10 +937,10 @@ int chunk_graph(lbm_ctx *c, bool scaled, hipGraphExec_t *out) {
       d.gs_ctr = c->gs_ctr;
       d.gs_j = j;
     }
-    err = c->ops->step(d, c->cap);
+    err = launch_steps(c, d, k, nullptr, c->cap);
     cur ^= 1;
   }
-  if (err == hipSuccess && scaled) err = lbm::graph_counter(c->gs_ctr, kGraphChunk, 0, c->cap);
+  if (err == hipSuccess && scaled) err = lbm::graph_counter(c->gs_ctr, chunk, 0, c->cap);
   hipGraph_t g = nullptr;
   const hipError_t ec = hipStreamEndCapture(c->cap, &g);
   if (err == hipSuccess) err = ec;
@@ -903,7 +954,7 @@ int chunk_graph(lbm_ctx *c, bool scaled, hipGraphExec_t *out) {
   return LBM_OK;
 }
 
-// n >= 2 kGraphChunk steps as graph replays plus the remainder launched one by one.
+// n >= 2 chunks of steps as graph replays plus the remainder launched directly.
 int graph_run(lbm_ctx *c, int64_t n, const double *g_scale) {
   const bool scaled = g_scale != nullptr;
   if (scaled) {
@@ -942,18 +993,14 @@ int graph_run(lbm_ctx *c, int64_t n, const double *g_scale) {
   int rc = chunk_graph(c, scaled, &e);
   if (rc) return rc;
   if (scaled) HIP_TRY(lbm::graph_counter(c->gs_ctr, 0, 1, c->stream));
-  const int64_t reps = n / kGraphChunk;
+  const int chunk = graph_chunk(c);
+  const int64_t reps = n / chunk;
   for (int64_t r = 0; r < reps; ++r) HIP_TRY(hipGraphLaunch(e, c->stream));
-  c->t += reps * kGraphChunk;  // kGraphChunk is even: the current buffer is unchanged
-  int64_t s = reps * kGraphChunk;
-  for (; s < n; ++s) {
-    const double sc = scaled ? g_scale[s] : 1.0;
-    HIP_TRY(c->ops->step(c->desc(sc), c->stream));
-    c->cur ^= 1;
-    c->t += 1;
-  }
-  c->last_scale = scaled ? g_scale[n - 1] : 1.0;
-  return LBM_OK;
+  // a chunk is an even number of launches: the current buffer is unchanged
+  const int64_t s = reps * chunk;
+  c->t += s;
+  if (s > 0) c->last_scale = scaled ? g_scale[s - 1] : 1.0;
+  return eager_steps(c, n - s, scaled ? g_scale + s : nullptr);
 }
 
 }  // namespace
@@ -974,25 +1021,23 @@ int lbm_step(lbm_ctx *c, int64_t n, const double *g_scale) {
     return rc ? rc : seen;
   }
   const int K = c->p.monitor_every;
-  const size_t pop_bytes = (size_t)c->Q * c->N * storage_bytes(c->p.storage);
-  for (int64_t s = 0; s < n; ++s) {
-    const double sc = g_scale ? g_scale[s] : 1.0;
-    if (c->p.debug_poison) HIP_TRY(lbm::fill_nan(c->buf[c->cur ^ 1], pop_bytes, c->stream));
-    lbm::LaunchDesc d = c->desc(sc);
-    HIP_TRY(c->ops->step(d, c->stream));
-    c->cur ^= 1;
-    c->t += 1;
-    c->last_scale = sc;
-    if (K > 0) {
-      if (c->t % K == 0) {
-        int rc = in_step_check(c);
-        if (rc) return rc;
-      } else if ((c->t + 1) % K == 0) {
-        // the velocity of the step before a check, for its residual
-        int rc = refresh_monitors(c, 2 /* record */);
-        if (rc) return rc;
-        c->uprev_time = c->t;
-      }
+  if (K <= 0) {
+    const int rc = eager_steps(c, n, g_scale);
+    return rc ? rc : seen;
+  }
+  for (int64_t s = 0; s < n;) {
+    // up to the next record: at the multiples of K and, for their residual, one step before
+    const int64_t to_check = K - c->t % K;
+    const int64_t run = std::min(n - s, to_check > 1 ? to_check - 1 : to_check);
+    int rc = eager_steps(c, run, g_scale ? g_scale + s : nullptr);
+    if (rc) return rc;
+    s += run;
+    if (c->t % K == 0) {
+      if ((rc = in_step_check(c))) return rc;
+    } else if ((c->t + 1) % K == 0) {
+      // the velocity of the step before a check, for its residual
+      if ((rc = refresh_monitors(c, 2 /* record */))) return rc;
+      c->uprev_time = c->t;
     }
   }
   return seen;
