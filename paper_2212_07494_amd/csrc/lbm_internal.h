@@ -101,6 +101,16 @@ inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
   return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
 }
 
+// Fourier waves for waves_kernel (device arrays), sorted into groups of one k_x: group g's
+// waves are [group_start[g], group_start[g + 1]) and its wavenumber group_k[g]; per wave k_y
+// and k_z (kyz), the phase, and the Q amplitudes' (re, im) pairs.  Wavenumbers are reduced to
+// [0, n_a).
+struct WaveTable {
+  int ngroups;
+  const int *group_start, *group_k, *kyz;
+  const double *phase, *amp;
+};
+
 // One launch of the batched engine's persistent kernels.
 struct BatchLaunch {
   int coll, storage, variant;
@@ -148,10 +158,8 @@ struct LatticeOps {
   void (*solid_words)(const uint8_t *solid, int nx, int ny, int nz, const int wall[3],
                       uint32_t *out);
   hipError_t (*scatter)(const LaunchDesc &, const double *in, hipStream_t);
-  // State from nw Fourier waves about the rest state of density base (waves_kernel;
-  // device arrays k: nw x 3, phase: nw, amp: nw x Q x 2)
-  hipError_t (*waves)(const LaunchDesc &, int nw, const int *k, const double *phase,
-                      const double *amp, double base, hipStream_t);
+  // State from Fourier waves about the rest state of density base (waves_kernel)
+  hipError_t (*waves)(const LaunchDesc &, const WaveTable &, double base, hipStream_t);
   hipError_t (*moments)(const LaunchDesc &, double *rho, double *u, void *uprev, int mode,
                         double *partials, hipStream_t);
   hipError_t (*batch_step)(const BatchLaunch &, hipStream_t);
@@ -196,6 +204,11 @@ inline const LatticeOps &ops_for(int lattice) {
     default: return ops_d3q27();
   }
 }
+
+// lbm_runtime.hip: host side of a WaveTable (arrays of the sizes lbm_set_waves packs).
+int sort_waves(int n, int Q, const int32_t *k, const double *phase, const double *amp, int nx,
+               int ny, int nz, double *amp_out, double *phase_out, int *kyz, int *start,
+               int *group_k);
 
 // Error reporting shared by the runtime units (lbm_runtime.hip): records the message
 // for lbm_last_error() and returns status.

@@ -376,42 +376,107 @@ __global__ void __launch_bounds__(256) scatter_kernel(S *__restrict__ f, Geom ge
 
 // State from a sum of Fourier waves about rest: f-bar_i(x) = w_i rho0 + sum_w
 // Re[A_wi e^{i theta_w(x)}], theta_w(x) = 2 pi sum_a k_wa x_a / n_a + phase_w, stored as
-// f-bar_i - w_i shift, rounded once from binary64.  k_wa x_a is reduced modulo n_a in
-// integers first, so the angle stays within a few periods at any size.  amp holds the
-// (re, im) pairs of wave w's Q amplitudes at 2 (w Q + i).
+// f-bar_i - w_i shift, rounded once from binary64.
+//
+// The phase factors are products, e^{i theta} = e^{2 pi i k_x x / nx} e^{i psi}, psi = 2 pi
+// (k_y y / ny + k_z z / nz) + phase, and the waves come sorted by k_x (WaveTable), so the sum
+// over the waves of one k_x is taken once per row of nodes: B_gi = sum_{w in g} A_wi
+// e^{i psi_w}, and a node adds Re[B_gi e^{2 pi i k_g x / nx}] per group g.  The host folds
+// k_x and nx - k_x into one group (the real part of a wave is that of its conjugate), so an
+// expansion to fourth order with |k| <= 4 per mode has at most 17 groups for its 185 waves.
+// k_a x_a is reduced modulo n_a in integers, so no angle is large.
+//
+// A workgroup takes WV_ROWS rows, one per wavefront, of WV_X nodes, two per lane.  For WV_G
+// groups at a time: their factors along x into LDS; the factors e^{i psi} of WV_SUB waves at a
+// time into LDS and from them the B_gi in registers (a thread holds one (g, i) for some of
+// the rows, so an amplitude is read once per WV_ROWS / PARTS rows); then the nodes' sums, B by
+// broadcast.  With one sincos and 4 Q operations a wave and node (the sum as written) the
+// 128^3 D3Q27 start of 185 waves took 4.0 ms, bound by the binary64 ALU; grouped it is bound
+// by writing the populations and the B_gi.
+constexpr int WV_ROWS = 8, WV_X = 128, WV_G = 8, WV_SUB = 32, WV_THREADS = 512;
+
 template <class L, class S>
-__global__ void __launch_bounds__(256) waves_kernel(S *__restrict__ f, Geom geo, int nw,
-                                                    const int *__restrict__ k,
-                                                    const double *__restrict__ phase,
-                                                    const double *__restrict__ amp,
-                                                    double base) {
-  const int64_t node = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (node >= geo.N) return;
-  const int n = (int)node;
-  const int x = n % geo.nx;
-  const int y = (n / geo.nx) % geo.ny;
-  const int z = n / (geo.nx * geo.ny);
-  const uint32_t sm = node_mask(geo, n);
-  if (sm & SOLID_NODE) return;
+__global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Geom geo,
+                                                           WaveTable t, double base) {
+  constexpr int Q = L::Q, PAIRS = WV_G * Q;
+  constexpr int PARTS = 4 * PAIRS <= WV_THREADS ? 4 : (2 * PAIRS <= WV_THREADS ? 2 : 1);
+  constexpr int PR = WV_ROWS / PARTS;  // rows of a thread's B_gi
+  static_assert(PAIRS * PARTS <= WV_THREADS && WV_THREADS == 64 * WV_ROWS && WV_X == 128);
+  __shared__ double2 ex[WV_G][WV_X], epsi[WV_SUB][WV_ROWS], B[WV_ROWS][WV_G][Q];
   const double two_pi = 6.283185307179586;
-  double acc[L::Q];
-  for (int i = 0; i < L::Q; ++i) acc[i] = 0.0;
-  for (int w = 0; w < nw; ++w) {
-    const int mx = (int)(((int64_t)k[3 * w] * x) % geo.nx);
-    const int my = (int)(((int64_t)k[3 * w + 1] * y) % geo.ny);
-    const int mz = (int)(((int64_t)k[3 * w + 2] * z) % geo.nz);
-    const double t = (double(mx) / geo.nx + double(my) / geo.ny) + double(mz) / geo.nz;
-    double s, c;
-    sincos(two_pi * t + phase[w], &s, &c);
-    const double *a = amp + (int64_t)2 * L::Q * w;
-    static_for<L::Q>([&](auto I) {
-      constexpr int i = decltype(I)::value;
-      acc[i] = acc[i] + (a[2 * i] * c - a[2 * i + 1] * s);
-    });
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nchunk = (geo.nx + WV_X - 1) / WV_X;
+  const int rows = geo.ny * geo.nz;
+  const int row0 = (int)(blockIdx.x / nchunk) * WV_ROWS;
+  const int x0 = (int)(blockIdx.x % nchunk) * WV_X;
+  const int part = tid / PAIRS, pg = (tid - part * PAIRS) / Q, pi = (tid - part * PAIRS) % Q;
+  double acc[2][Q];
+  for (int i = 0; i < Q; ++i) acc[0][i] = acc[1][i] = 0.0;
+  for (int g0 = 0; g0 < t.ngroups; g0 += WV_G) {
+    const int gn = min(WV_G, t.ngroups - g0);
+    for (int j = tid; j < gn * WV_X; j += WV_THREADS) {
+      const int g = j / WV_X, x = x0 + j % WV_X;
+      const int m = (int)(((int64_t)t.group_k[g0 + g] * x) % geo.nx);
+      double s, c;
+      sincos(two_pi * (double(m) / geo.nx), &s, &c);
+      ex[g][j % WV_X] = make_double2(c, s);
+    }
+    double br[PR], bi[PR];
+    for (int r = 0; r < PR; ++r) br[r] = bi[r] = 0.0;
+    const int wlo = t.group_start[g0], whi = t.group_start[g0 + gn];
+    const bool holds = part < PARTS && pg < gn;
+    const int glo = holds ? t.group_start[g0 + pg] : 0, ghi = holds ? t.group_start[g0 + pg + 1] : 0;
+    for (int w0 = wlo; w0 < whi; w0 += WV_SUB) {
+      __syncthreads();
+      for (int j = tid; j < WV_SUB * WV_ROWS; j += WV_THREADS) {
+        const int w = w0 + j / WV_ROWS, row = min(row0 + j % WV_ROWS, rows - 1);
+        if (w < whi) {
+          const int y = row % geo.ny, z = row / geo.ny;
+          const int my = (int)(((int64_t)t.kyz[2 * w] * y) % geo.ny);
+          const int mz = (int)(((int64_t)t.kyz[2 * w + 1] * z) % geo.nz);
+          double s, c;
+          sincos(two_pi * (double(my) / geo.ny + double(mz) / geo.nz) + t.phase[w], &s, &c);
+          epsi[j / WV_ROWS][j % WV_ROWS] = make_double2(c, s);
+        }
+      }
+      __syncthreads();
+      for (int w = max(w0, glo); w < min(w0 + WV_SUB, ghi); ++w) {
+        const double2 a = reinterpret_cast<const double2 *>(t.amp)[(int64_t)w * Q + pi];
+        for (int r = 0; r < PR; ++r) {
+          const double2 e = epsi[w - w0][part * PR + r];
+          br[r] = fmadd(a.x, e.x, fmadd(-a.y, e.y, br[r]));
+          bi[r] = fmadd(a.x, e.y, fmadd(a.y, e.x, bi[r]));
+        }
+      }
+    }
+    if (holds)
+      for (int r = 0; r < PR; ++r) B[part * PR + r][pg][pi] = make_double2(br[r], bi[r]);
+    __syncthreads();
+    for (int g = 0; g < gn; ++g) {
+      const double2 e0 = ex[g][lane], e1 = ex[g][lane + 64];
+      static_for<Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const double2 b = B[wave][g][i];
+        acc[0][i] = fmadd(b.x, e0.x, fmadd(-b.y, e0.y, acc[0][i]));
+        acc[1][i] = fmadd(b.x, e1.x, fmadd(-b.y, e1.y, acc[1][i]));
+      });
+    }
+    __syncthreads();
   }
-  static_for<L::Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    f[pull_slot<L, i>(x, y, z, geo, sm)] = S(Tab<L, double>::w(i) * base + acc[i]);
+  const int row = row0 + wave;
+  if (row >= rows) return;
+  const int y = row % geo.ny, z = row / geo.ny;
+  static_for<2>([&](auto J) {
+    constexpr int j = decltype(J)::value;
+    const int x = x0 + lane + 64 * j;
+    if (x >= geo.nx) return;
+    const uint32_t sm = node_mask(geo, row * geo.nx + x);
+    if (sm & SOLID_NODE) return;
+    static_for<Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      f[pull_slot<L, i>(x, y, z, geo, sm)] = S(Tab<L, double>::w(i) * base + acc[j][i]);
+    });
   });
 }
 

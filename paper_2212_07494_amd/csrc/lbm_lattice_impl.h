@@ -167,13 +167,13 @@ struct Ops {
       return hipGetLastError();
     });
   }
-  static hipError_t waves(const LaunchDesc &d, int nw, const int *k, const double *phase,
-                          const double *amp, double base, hipStream_t s) {
+  static hipError_t waves(const LaunchDesc &d, const WaveTable &t, double base, hipStream_t s) {
     return with_types(d.storage, [&](auto *sp, auto *) -> hipError_t {
       using S = std::remove_pointer_t<decltype(sp)>;
-      const unsigned blocks = (unsigned)((d.geo.N + 255) / 256);
-      hipLaunchKernelGGL((waves_kernel<L, S>), dim3(blocks), dim3(256), 0, s,
-                         static_cast<S *>(d.fout), geom_of(d), nw, k, phase, amp, base);
+      const int64_t rows = (int64_t)d.geo.ny * d.geo.nz;
+      const int64_t blocks = (rows + WV_ROWS - 1) / WV_ROWS * ((d.geo.nx + WV_X - 1) / WV_X);
+      hipLaunchKernelGGL((waves_kernel<L, S>), dim3((unsigned)blocks), dim3(WV_THREADS), 0, s,
+                         static_cast<S *>(d.fout), geom_of(d), t, base);
       return hipGetLastError();
     });
   }

@@ -11,6 +11,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "lbm.h"
@@ -414,6 +415,47 @@ void release(lbm_ctx *c) {
 }
 
 }  // namespace
+
+// The waves of a WaveTable on the host: folded (a wave whose k_x exceeds nx - k_x becomes its
+// conjugate, k, phase and imaginary parts negated, with the same real part), sorted by k_x.
+// Returns the number of groups, -1 if memory ran out.
+int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const double *amp,
+                    int nx, int ny, int nz, double *amp_out, double *phase_out, int *kyz,
+                    int *start, int *group_k) {
+  const int dims[3] = {nx, ny, nz};
+  auto reduced = [&](int w, int a, bool neg) {
+    const int64_t m = ((int64_t)k[3 * w + a] % dims[a] + dims[a]) % dims[a];
+    return (int)(neg && m ? dims[a] - m : m);
+  };
+  std::vector<std::pair<int, int>> order;  // folded k_x, wave
+  try {
+    order.reserve(n);
+  } catch (const std::bad_alloc &) {
+    return -1;
+  }
+  for (int w = 0; w < n; ++w)
+    order.emplace_back(std::min(reduced(w, 0, false), reduced(w, 0, true)), w);
+  std::sort(order.begin(), order.end());
+  int g = 0;
+  for (int j = 0; j < n; ++j) {
+    const int w = order[j].second;
+    const bool neg = reduced(w, 0, false) != order[j].first;
+    if (j == 0 || order[j].first != order[j - 1].first) {
+      start[g] = j;
+      group_k[g++] = order[j].first;
+    }
+    kyz[2 * j] = reduced(w, 1, neg);
+    kyz[2 * j + 1] = reduced(w, 2, neg);
+    phase_out[j] = neg ? -phase[w] : phase[w];
+    for (int i = 0; i < Q; ++i) {
+      amp_out[2 * ((size_t)j * Q + i)] = amp[2 * ((size_t)w * Q + i)];
+      const double im = amp[2 * ((size_t)w * Q + i) + 1];
+      amp_out[2 * ((size_t)j * Q + i) + 1] = neg ? -im : im;
+    }
+  }
+  start[g] = n;
+  return g;
+}
 
 // Monitor finalisation, the NaN fill and the stream-copy probe (lbm_aux.hip).
 namespace lbm {
@@ -1168,24 +1210,33 @@ int lbm_set_waves(lbm_ctx *c, int32_t nwaves, const int32_t *k, const double *ph
     if (!std::isfinite(amp[j])) return fail(LBM_EINVAL, "amp[%lld] is not finite", (long long)j);
   for (int w = 0; w < nwaves; ++w)
     if (!std::isfinite(phase[w])) return fail(LBM_EINVAL, "phase[%d] is not finite", w);
-  // device copies: amp (binary64), phase, then k (int32)
-  const size_t ab = (size_t)2 * c->Q * nwaves * sizeof(double);
-  const size_t pb = (size_t)nwaves * sizeof(double);
-  const size_t kb = (size_t)3 * nwaves * sizeof(int32_t);
-  int rc = c->need_scratch(ab + pb + kb + 8);
-  if (rc) return rc;
-  char *base = static_cast<char *>(c->scratch);
-  double *amp_d = reinterpret_cast<double *>(base);
-  double *phase_d = reinterpret_cast<double *>(base + ab);
-  int32_t *k_d = reinterpret_cast<int32_t *>(base + ab + pb);
-  if (nwaves > 0) {
-    HIP_TRY(hipMemcpyAsync(amp_d, amp, ab, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(phase_d, phase, pb, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(hipMemcpyAsync(k_d, k, kb, hipMemcpyHostToDevice, c->stream));
+  // sorted by k_x and folded (WaveTable), packed for one copy: amp, phase (binary64), then
+  // kyz, the groups' starts and their k_x (int32)
+  const size_t na = (size_t)2 * c->Q * nwaves, nd = na + nwaves, ni = (size_t)4 * nwaves + 1;
+  std::vector<double> pack;
+  try {
+    pack.resize(nd + (ni + 1) / 2);
+  } catch (const std::bad_alloc &) {
+    return fail(LBM_ENOMEM, "host copy of %d waves", (int)nwaves);
   }
+  double *amp_h = pack.data(), *phase_h = amp_h + na;
+  int *kyz_h = reinterpret_cast<int *>(amp_h + nd);
+  int *start_h = kyz_h + 2 * nwaves, *gk_h = start_h + nwaves + 1;
+  const int ngroups = lbm::sort_waves(nwaves, c->Q, k, phase, amp, c->p.nx, c->p.ny, c->p.nz,
+                                      amp_h, phase_h, kyz_h, start_h, gk_h);
+  if (ngroups < 0) return fail(LBM_ENOMEM, "sorting %d waves", (int)nwaves);
+  int rc = c->need_scratch(pack.size() * sizeof(double));
+  if (rc) return rc;
+  double *amp_d = static_cast<double *>(c->scratch);
+  const int *kyz_d = reinterpret_cast<const int *>(amp_d + nd);
+  const lbm::WaveTable tab = {ngroups, kyz_d + 2 * nwaves, kyz_d + 3 * nwaves + 1,
+                              kyz_d,   amp_d + na,         amp_d};
+  if (nwaves > 0)
+    HIP_TRY(hipMemcpyAsync(amp_d, pack.data(), pack.size() * sizeof(double),
+                           hipMemcpyHostToDevice, c->stream));
   lbm::LaunchDesc d = c->desc(1.0);
   d.fout = c->buf[c->cur];
-  HIP_TRY(c->ops->waves(d, nwaves, k_d, phase_d, amp_d, c->p.rho0 - c->shift, c->stream));
+  HIP_TRY(c->ops->waves(d, tab, c->p.rho0 - c->shift, c->stream));
   // the host arrays may be released once this returns
   HIP_TRY(hipStreamSynchronize(c->stream));
   c->t = 0;
