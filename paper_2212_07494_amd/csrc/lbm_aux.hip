@@ -11,29 +11,23 @@ namespace {
 constexpr int kSlots = MON_SLOTS;  // the monitor record's slots (lbm_internal.h)
 constexpr int kUmax = MON_UMAX;
 
-// Sum the per-block partials in a fixed order (one block of 256 threads): thread k
-// folds blocks k, k + 256, ... in turn, then a fixed binary tree combines the threads.
-// The result is deterministic for a given block count.
-__global__ void __launch_bounds__(256) finalize_kernel(const double *partials, int64_t nb,
-                                                       double *out) {
-  __shared__ double red[256];
-  for (int s = 0; s < kSlots; ++s) {
-    double acc = 0.0;
-    for (int64_t b = threadIdx.x; b < nb; b += 256) {
-      const double t = partials[b * kSlots + s];
-      acc = (s == kUmax) ? fmax(acc, t) : acc + t;
-    }
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-      if ((int)threadIdx.x < o)
-        red[threadIdx.x] = (s == kUmax) ? fmax(red[threadIdx.x], red[threadIdx.x + o])
-                                        : red[threadIdx.x] + red[threadIdx.x + o];
-      __syncthreads();
-    }
-    if (threadIdx.x == 0) out[s] = red[0];
-    __syncthreads();
+// Sum the per-block partials in a fixed order: wavefront s takes slot s, lane l the blocks l,
+// l + 64, ... in turn, then a fixed tree combines the lanes.  The result is deterministic
+// for a given block count.
+__global__ void __launch_bounds__(64 * kSlots) finalize_kernel(const double *partials, int64_t nb,
+                                                               double *out) {
+  const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  double acc = 0.0;
+#pragma unroll 8
+  for (int64_t b = lane; b < nb; b += 64) {
+    const double t = partials[b * kSlots + s];
+    acc = (s == kUmax) ? fmax(acc, t) : acc + t;
   }
+  for (int o = 32; o > 0; o >>= 1) {
+    const double t = __shfl_xor(acc, o, 64);
+    acc = (s == kUmax) ? fmax(acc, t) : acc + t;
+  }
+  if (lane == 0) out[s] = acc;
 }
 
 // Copy variants (16-byte vectors):
@@ -183,7 +177,7 @@ hipError_t fill_nan(void *p, size_t bytes, hipStream_t s) {
 }
 
 hipError_t finalize_monitors(const double *partials, int64_t nb, double *out, hipStream_t s) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(256), 0, s, partials, nb, out);
+  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64 * kSlots), 0, s, partials, nb, out);
   return hipGetLastError();
 }
 

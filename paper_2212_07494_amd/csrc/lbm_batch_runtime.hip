@@ -654,7 +654,7 @@ int lbm_batch_moments(lbm_batch *b, int32_t dom, double *rho, double *u) {
   if (rc) return rc;
   double *rho_d = static_cast<double *>(b->scratch);
   double *u_d = reinterpret_cast<double *>(static_cast<char *>(b->scratch) + fld);
-  HIP_TRY(b->ops->moments(b->desc(dom), rho_d, u_d, nullptr, 1, nullptr, b->stream));
+  HIP_TRY(b->ops->moments(b->desc(dom), rho_d, u_d, b->stream));
   if (rho) HIP_TRY(hipMemcpyAsync(rho, rho_d, fld, hipMemcpyDeviceToHost, b->stream));
   if (u) HIP_TRY(hipMemcpyAsync(u, u_d, fld * b->D, hipMemcpyDeviceToHost, b->stream));
   HIP_TRY(hipStreamSynchronize(b->stream));

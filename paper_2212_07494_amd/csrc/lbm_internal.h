@@ -160,8 +160,11 @@ struct LatticeOps {
   hipError_t (*scatter)(const LaunchDesc &, const double *in, hipStream_t);
   // State from Fourier waves about the rest state of density base (waves_kernel)
   hipError_t (*waves)(const LaunchDesc &, const WaveTable &, double base, hipStream_t);
-  hipError_t (*moments)(const LaunchDesc &, double *rho, double *u, void *uprev, int mode,
-                        double *partials, hipStream_t);
+  hipError_t (*moments)(const LaunchDesc &, double *rho, double *u, hipStream_t);
+  // monitor partials (MON_SLOTS a block, monitor_blocks blocks); mode 2 record, 4 compare and
+  // record (uprev: the recorded velocities)
+  hipError_t (*monitor)(const LaunchDesc &, void *uprev, int mode, double *partials,
+                        hipStream_t);
   hipError_t (*batch_step)(const BatchLaunch &, hipStream_t);
   hipError_t (*batch_monitor)(const BatchLaunch &, hipStream_t);
   // k steps (odd, at least 3) of every active domain in one launch; NULL as for multi
@@ -213,6 +216,16 @@ int sort_waves(int n, int Q, const int32_t *k, const double *phase, const double
 // Error reporting shared by the runtime units (lbm_runtime.hip): records the message
 // for lbm_last_error() and returns status.
 int set_error(int status, const char *fmt, ...);
+
+// Blocks of the monitor pass: one per tile of bx x by nodes, at most eight a compute unit.
+constexpr int MONITOR_BLOCKS = 2048;
+inline int64_t monitor_tiles(const LaunchDesc &d) {
+  return (int64_t)((d.geo.nx + d.bx - 1) / d.bx) * ((d.geo.ny + d.by - 1) / d.by) * d.geo.nz;
+}
+inline int64_t monitor_blocks(const LaunchDesc &d) {
+  const int64_t t = monitor_tiles(d);
+  return t < MONITOR_BLOCKS ? t : MONITOR_BLOCKS;
+}
 
 inline dim3 grid_of(const LaunchDesc &d) {
   return dim3((d.geo.nx + d.bx - 1) / d.bx, (d.geo.ny + d.by - 1) / d.by, d.geo.nz);

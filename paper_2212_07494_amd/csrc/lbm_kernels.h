@@ -391,9 +391,18 @@ __global__ void __launch_bounds__(256) scatter_kernel(S *__restrict__ f, Geom ge
 // time into LDS and from them the B_gi in registers (a thread holds one (g, i) for some of
 // the rows, so an amplitude is read once per WV_ROWS / PARTS rows); then the nodes' sums, B by
 // broadcast.  With one sincos and 4 Q operations a wave and node (the sum as written) the
-// 128^3 D3Q27 start of 185 waves took 4.0 ms, bound by the binary64 ALU; grouped it is bound
-// by writing the populations and the B_gi.
-constexpr int WV_ROWS = 8, WV_X = 128, WV_G = 8, WV_SUB = 32, WV_THREADS = 512;
+// 128^3 D3Q27 start of 185 waves (9 groups) took 4.04 ms, bound by the binary64 ALU; grouped
+// 0.52 ms, of which writing the populations needs 0.07.  One workgroup of eight wavefronts fits a
+// compute unit (206 VGPRs), so its phases do not overlap; 256 threads and four rows, with
+// two workgroups, took the same time.
+constexpr int WV_ROWS = 8, WV_X = 128, WV_G = 8, WV_SUB = 64, WV_THREADS = 512;
+
+// k x mod n for 0 <= k, x and k < n (x may run past n by less than WV_X): in 32 bits where
+// the product fits.
+__device__ __forceinline__ int wave_mod(int k, int x, int n) {
+  if (n <= 65000) return (int)((uint32_t)k * (uint32_t)x % (uint32_t)n);
+  return (int)((int64_t)k * x % n);
+}
 
 template <class L, class S>
 __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Geom geo,
@@ -417,7 +426,7 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
     const int gn = min(WV_G, t.ngroups - g0);
     for (int j = tid; j < gn * WV_X; j += WV_THREADS) {
       const int g = j / WV_X, x = x0 + j % WV_X;
-      const int m = (int)(((int64_t)t.group_k[g0 + g] * x) % geo.nx);
+      const int m = wave_mod(t.group_k[g0 + g], x, geo.nx);
       double s, c;
       sincos(two_pi * (double(m) / geo.nx), &s, &c);
       ex[g][j % WV_X] = make_double2(c, s);
@@ -433,15 +442,17 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
         const int w = w0 + j / WV_ROWS, row = min(row0 + j % WV_ROWS, rows - 1);
         if (w < whi) {
           const int y = row % geo.ny, z = row / geo.ny;
-          const int my = (int)(((int64_t)t.kyz[2 * w] * y) % geo.ny);
-          const int mz = (int)(((int64_t)t.kyz[2 * w + 1] * z) % geo.nz);
+          const int my = wave_mod(t.kyz[2 * w], y, geo.ny);
+          const int mz = wave_mod(t.kyz[2 * w + 1], z, geo.nz);
           double s, c;
           sincos(two_pi * (double(my) / geo.ny + double(mz) / geo.nz) + t.phase[w], &s, &c);
           epsi[j / WV_ROWS][j % WV_ROWS] = make_double2(c, s);
         }
       }
       __syncthreads();
-      for (int w = max(w0, glo); w < min(w0 + WV_SUB, ghi); ++w) {
+      const int we = min(w0 + WV_SUB, ghi);
+#pragma unroll 4
+      for (int w = max(w0, glo); w < we; ++w) {
         const double2 a = reinterpret_cast<const double2 *>(t.amp)[(int64_t)w * Q + pi];
         for (int r = 0; r < PR; ++r) {
           const double2 e = epsi[w - w0][part * PR + r];
@@ -480,10 +491,7 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
   });
 }
 
-// ---- monitors -------------------------------------------------------------------------
-// Block partials use the monitor slots of lbm_internal.h (MON_*).
-enum { MOM_WRITE = 1, MOM_RECORD = 2, MOM_COMPARE = 4 };
-
+// ---- moments and monitors ---------------------------------------------------------------
 __device__ __forceinline__ double wave_sum(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
@@ -495,64 +503,99 @@ __device__ __forceinline__ double wave_max(double v) {
   return v;
 }
 
-// Density and physical velocity of the current state (pulled), optionally written out
-// (binary64), recorded into uprev, and reduced into per-block monitor partials.
+// Density and physical velocity of the current state at one node (pulled).
 template <class L, class S, class T, int GK>
-__global__ void __launch_bounds__(256) moments_kernel(StepArgs<T> a, double *rho_out,
-                                                      double *u_out, T *uprev, int mode,
-                                                      double *partials) {
-  const int x = blockIdx.x * blockDim.x + threadIdx.x;
-  const int y = blockIdx.y * blockDim.y + threadIdx.y;
-  const int z = blockIdx.z;
-  const bool inside = (x < a.geo.nx) && (y < a.geo.ny);
-  const int node = (z * a.geo.ny + y) * a.geo.nx + x;
-  const uint32_t sm = inside ? node_mask(a.geo, node) : 0u;
-  const bool live = inside && !(sm & SOLID_NODE);
-  double v[MON_SLOTS];
-  for (int s = 0; s < MON_SLOTS; ++s) v[s] = 0.0;
-  if (inside && !live && (mode & MOM_WRITE)) {  // solid node: no fluid
-    if (rho_out) rho_out[node] = 0.0;
-    if (u_out)
-      for (int c = 0; c < L::D; ++c) u_out[(int64_t)c * a.geo.N + node] = 0.0;
-  }
-  if (live) {
-    const int N = a.geo.N;
-    const S *__restrict__ fin = static_cast<const S *>(a.fin);
-    T d[L::Q];
+__device__ __forceinline__ Macro<T> node_moments(const StepArgs<T> &a, int x, int y, int z,
+                                                 int node, uint32_t sm, bool fast) {
+  const S *__restrict__ fin = static_cast<const S *>(a.fin);
+  T d[L::Q];
+  if (fast) {
+    static_for<L::Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      d[i] = load_as<S, T>(pull_ptr_periodic<L, i>(fin, x, y, z, a.geo));
+    });
+  } else {
     static_for<L::Q>([&](auto I) {
       constexpr int i = decltype(I)::value;
       d[i] = load_as<S, T>(fin + pull_slot<L, i>(x, y, z, a.geo, sm));
     });
-    T g[3];
-    load_force<T, GK>(a.force, x, y, z, node, N, L::D, g);
-    const Macro<T> M = macroscopic<L>(d, a.shift, g);
-    if (mode & MOM_WRITE) {
-      if (rho_out) rho_out[node] = double(M.rho);
-      if (u_out)
-        for (int c = 0; c < L::D; ++c) u_out[(int64_t)c * N + node] = double(M.u[c]);
-    }
+  }
+  T g[3];
+  load_force<T, GK>(a.force, x, y, z, node, a.geo.N, L::D, g);
+  return macroscopic<L>(d, a.shift, g);
+}
+
+// Density and physical velocity of every node in binary64 (0 at solid nodes).
+template <class L, class S, class T, int GK>
+__global__ void __launch_bounds__(256) moments_kernel(StepArgs<T> a, double *__restrict__ rho_out,
+                                                      double *__restrict__ u_out) {
+  const int x = blockIdx.x * blockDim.x + threadIdx.x;
+  const int y = blockIdx.y * blockDim.y + threadIdx.y;
+  const int z = blockIdx.z;
+  if (x >= a.geo.nx || y >= a.geo.ny) return;
+  const int node = (z * a.geo.ny + y) * a.geo.nx + x;
+  const uint32_t sm = node_mask(a.geo, node);
+  if (sm & SOLID_NODE) {  // no fluid
+    rho_out[node] = 0.0;
+    for (int c = 0; c < L::D; ++c) u_out[(int64_t)c * a.geo.N + node] = 0.0;
+    return;
+  }
+  const Macro<T> M = node_moments<L, S, T, GK>(a, x, y, z, node, sm, false);
+  rho_out[node] = double(M.rho);
+  for (int c = 0; c < L::D; ++c) u_out[(int64_t)c * a.geo.N + node] = double(M.u[c]);
+}
+
+// The monitor sums of the current state (MON_* of lbm_internal.h), per block, and its
+// velocities recorded into uprev (MOM_COMPARE: after comparing with the recorded ones).
+//
+// Bound by reading the populations once, if a node costs no more than its sums: the blocks
+// (at most MONITOR_BLOCKS) walk the lattice's tiles of blockDim nodes and reduce across lanes
+// once each.  Reducing every tile's eleven sums across lanes and leaving a record per tile
+// cost a monitor call 1,344 us at 256^3 D3Q19 FP32-shifted and 208 us at 128^3 D3Q27 FP64;
+// walking, 410 and 157 us (the second mostly its 0.55 GB and the record's way to the host).
+enum { MOM_RECORD = 2, MOM_COMPARE = 4 };
+
+template <class L, class S, class T, int GK>
+__global__ void __launch_bounds__(256) monitor_kernel(StepArgs<T> a, int ntx, int nty,
+                                                      int64_t ntiles, T *__restrict__ uprev,
+                                                      int mode, double *__restrict__ partials) {
+  double v[MON_SLOTS];  // MON_UMAX: the largest |u|^2
+  for (int s = 0; s < MON_SLOTS; ++s) v[s] = 0.0;
+  const int N = a.geo.N;
+  for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+    const int z = (int)(t / ((int64_t)ntx * nty));
+    const int ty = (int)(t / ntx) - z * nty;
+    const int x0 = (int)(t % ntx) * blockDim.x, y0 = ty * blockDim.y;
+    const int x = x0 + threadIdx.x, y = y0 + threadIdx.y;
+    if (x >= a.geo.nx || y >= a.geo.ny) continue;
+    const int node = (z * a.geo.ny + y) * a.geo.nx + x;
+    const uint32_t sm = node_mask(a.geo, node);
+    if (sm & SOLID_NODE) continue;
+    const bool fast = fast_block<S>(a.geo, x0, x0 + (int)blockDim.x - 1, y0,
+                                    y0 + (int)blockDim.y - 1, z);
+    const Macro<T> M = node_moments<L, S, T, GK>(a, x, y, z, node, sm, fast);
     const double r = double(M.rho);
     double u2 = 0, du2 = 0;
     for (int c = 0; c < L::D; ++c) {
       const double uc = double(M.u[c]);
       u2 += uc * uc;
-      v[MON_MX + c] = r * uc;
-      v[MON_JX + c] = double(M.j[c]);
+      v[MON_MX + c] += r * uc;
+      v[MON_JX + c] += double(M.j[c]);
+      T *up = uprev + (int64_t)c * N + node;
       if (mode & MOM_COMPARE) {
-        const double dd = uc - double(uprev[(int64_t)c * N + node]);
+        const double dd = uc - double(*up);
         du2 += dd * dd;
       }
-      if (mode & (MOM_RECORD | MOM_COMPARE)) uprev[(int64_t)c * N + node] = M.u[c];
+      *up = M.u[c];
     }
-    v[MON_MASS] = r;
-    v[MON_DU2] = du2;
-    v[MON_U2] = u2;
-    v[MON_UMAX] = sqrt(u2);
-    const bool bad = !isfinite(r) || !isfinite(u2);
-    v[MON_BAD] = bad ? 1.0 : 0.0;
-    if (bad) v[MON_UMAX] = 0;
+    v[MON_MASS] += r;
+    v[MON_DU2] += du2;
+    v[MON_U2] += u2;
+    if (!isfinite(r) || !isfinite(u2))
+      v[MON_BAD] += 1.0;
+    else
+      v[MON_UMAX] = fmax(v[MON_UMAX], u2);
   }
-  if (!partials) return;
   __shared__ double red[4][MON_SLOTS];
   const int tid = threadIdx.y * blockDim.x + threadIdx.x;
   const int wave = tid >> 6, lane = tid & 63;
@@ -565,8 +608,7 @@ __global__ void __launch_bounds__(256) moments_kernel(StepArgs<T> a, double *rho
     const int nw = (blockDim.x * blockDim.y + 63) >> 6;
     double acc = red[0][tid];
     for (int w = 1; w < nw; ++w) acc = (tid == MON_UMAX) ? fmax(acc, red[w][tid]) : acc + red[w][tid];
-    const int64_t b = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
-    partials[b * MON_SLOTS + tid] = acc;
+    partials[(int64_t)blockIdx.x * MON_SLOTS + tid] = (tid == MON_UMAX) ? sqrt(acc) : acc;
   }
 }
 

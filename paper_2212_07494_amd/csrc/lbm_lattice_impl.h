@@ -177,20 +177,36 @@ struct Ops {
       return hipGetLastError();
     });
   }
-  template <class S, class T, int GK>
-  static hipError_t moments_t(const LaunchDesc &d, double *rho, double *u, void *uprev, int mode,
-                              double *partials, hipStream_t s) {
-    hipLaunchKernelGGL((moments_kernel<L, S, T, GK>), grid_of(d), dim3(d.bx, d.by), 0, s,
-                       make_args<T>(d), rho, u, static_cast<T *>(uprev), mode, partials);
-    return hipGetLastError();
-  }
-  static hipError_t moments(const LaunchDesc &d, double *rho, double *u, void *uprev, int mode,
-                            double *partials, hipStream_t s) {
+  static hipError_t moments(const LaunchDesc &d, double *rho, double *u, hipStream_t s) {
     return with_types(d.storage, [&](auto *sp, auto *tp) -> hipError_t {
       using S = std::remove_pointer_t<decltype(sp)>;
       using T = std::remove_pointer_t<decltype(tp)>;
-      return d.gk ? moments_t<S, T, GK_FIELD>(d, rho, u, uprev, mode, partials, s)
-                  : moments_t<S, T, GK_PROFILE>(d, rho, u, uprev, mode, partials, s);
+      if (d.gk)
+        hipLaunchKernelGGL((moments_kernel<L, S, T, GK_FIELD>), grid_of(d), dim3(d.bx, d.by), 0,
+                           s, make_args<T>(d), rho, u);
+      else
+        hipLaunchKernelGGL((moments_kernel<L, S, T, GK_PROFILE>), grid_of(d), dim3(d.bx, d.by),
+                           0, s, make_args<T>(d), rho, u);
+      return hipGetLastError();
+    });
+  }
+  static hipError_t monitor(const LaunchDesc &d, void *uprev, int mode, double *partials,
+                            hipStream_t s) {
+    const dim3 g = grid_of(d);
+    const int64_t ntiles = monitor_tiles(d);
+    const dim3 grid((unsigned)monitor_blocks(d));
+    return with_types(d.storage, [&](auto *sp, auto *tp) -> hipError_t {
+      using S = std::remove_pointer_t<decltype(sp)>;
+      using T = std::remove_pointer_t<decltype(tp)>;
+      if (d.gk)
+        hipLaunchKernelGGL((monitor_kernel<L, S, T, GK_FIELD>), grid, dim3(d.bx, d.by), 0, s,
+                           make_args<T>(d), (int)g.x, (int)g.y, ntiles, static_cast<T *>(uprev),
+                           mode, partials);
+      else
+        hipLaunchKernelGGL((monitor_kernel<L, S, T, GK_PROFILE>), grid, dim3(d.bx, d.by), 0, s,
+                           make_args<T>(d), (int)g.x, (int)g.y, ntiles, static_cast<T *>(uprev),
+                           mode, partials);
+      return hipGetLastError();
     });
   }
   template <int COLL, class S, class T, int MEM>
@@ -250,6 +266,7 @@ const LatticeOps &LBM_OPS() {
                                  &impl::Ops<LBM_LAT>::scatter,
                                  &impl::Ops<LBM_LAT>::waves,
                                  &impl::Ops<LBM_LAT>::moments,
+                                 &impl::Ops<LBM_LAT>::monitor,
                                  &impl::Ops<LBM_LAT>::batch_step,
                                  &impl::Ops<LBM_LAT>::batch_monitor,
                                  LBM_BATCH_MULTI};

@@ -165,8 +165,7 @@ struct lbm_ctx {
   std::vector<uint32_t> smask_host;       // the same on the host (upload source, identity)
   void *uprev = nullptr;
   int64_t uprev_time = -2;
-  double *partials = nullptr;
-  int64_t nblocks = 0, nblocks_cap = 0;  // blocks of the current grid; partials' capacity
+  double *partials = nullptr;  // of the monitor pass (MONITOR_BLOCKS records)
   double *mon_dev = nullptr;
   // In-step monitor checks (monitor_every > 0): the device record of time dev_step (-1:
   // none) and its mode; the latest check's copy in pinned host memory (mon_host) with the
@@ -470,8 +469,8 @@ namespace {
 
 int refresh_monitors(lbm_ctx *c, int mode) {
   lbm::LaunchDesc d = c->desc(c->last_scale);
-  HIP_TRY(c->ops->moments(d, nullptr, nullptr, c->uprev, mode, c->partials, c->stream));
-  HIP_TRY(lbm::finalize_monitors(c->partials, c->nblocks, c->mon_dev, c->stream));
+  HIP_TRY(c->ops->monitor(d, c->uprev, mode, c->partials, c->stream));
+  HIP_TRY(lbm::finalize_monitors(c->partials, lbm::monitor_blocks(d), c->mon_dev, c->stream));
   return LBM_OK;
 }
 
@@ -784,10 +783,6 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
   if (c->ops->multi && !p->debug_poison)
     c->multi = lbm::multi_plan(p->nx, p->ny, p->bc[1] == LBM_WALLS, storage_bytes(p->storage),
                                c->lds_cu, ncu);
-  const dim3 grid((p->nx + c->bx - 1) / c->bx, (p->ny + c->by - 1) / c->by, p->nz);
-  c->nblocks = (int64_t)grid.x * grid.y * grid.z;
-  c->nblocks_cap = c->nblocks;
-
   const size_t pop_bytes = (size_t)c->Q * (size_t)c->N * storage_bytes(p->storage);
   const size_t ab = arith_bytes(p->storage);
   // force table, in the arithmetic type
@@ -834,7 +829,7 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
       (p->solid && (rc = c->dalloc((void **)&c->smask, (size_t)c->N * sizeof(uint32_t)))) ||
       (rc = c->dalloc(&c->uprev, 3 * (size_t)c->N * ab)) ||
       (rc = c->dalloc((void **)&c->partials,
-                      (size_t)c->nblocks * lbm::MON_SLOTS * sizeof(double))) ||
+                      (size_t)lbm::MONITOR_BLOCKS * lbm::MON_SLOTS * sizeof(double))) ||
       (rc = c->dalloc((void **)&c->mon_dev, lbm::MON_SLOTS * sizeof(double)))) {
     std::string msg = g_last_error;
     release(c);
@@ -1120,7 +1115,7 @@ int lbm_moments(lbm_ctx *c, double g_scale, double *rho, double *u) {
   double *rho_d = static_cast<double *>(c->scratch);
   double *u_d = reinterpret_cast<double *>(static_cast<char *>(c->scratch) + fld);
   lbm::LaunchDesc d = c->desc(g_scale);
-  HIP_TRY(c->ops->moments(d, rho_d, u_d, nullptr, 1, nullptr, c->stream));
+  HIP_TRY(c->ops->moments(d, rho_d, u_d, c->stream));
   if (rho) HIP_TRY(hipMemcpyAsync(rho, rho_d, fld, hipMemcpyDeviceToHost, c->stream));
   if (u) HIP_TRY(hipMemcpyAsync(u, u_d, fld * c->D, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1470,20 +1465,6 @@ int lbm_set_tuning(lbm_ctx *c, const lbm_tuning *t) {
   if (!valid(c)) return fail(LBM_ESTATE, "invalid context");
   if (!tuning_ok(t)) return fail(LBM_EINVAL, "invalid tuning");
   if (t->by > 65535) return fail(LBM_EINVAL, "invalid tuning");
-  // the monitor partials are sized by the block grid: a larger buffer is allocated
-  // before anything changes, so a failure leaves the context as it was
-  const int64_t nb = (int64_t)((c->p.nx + t->bx - 1) / t->bx) * ((c->p.ny + t->by - 1) / t->by) *
-                     c->p.nz;
-  if (nb > c->nblocks_cap) {
-    double *grown = nullptr;
-    int rc = c->dalloc((void **)&grown, (size_t)nb * lbm::MON_SLOTS * sizeof(double));
-    if (rc) return rc;
-    HIP_TRY(hipStreamSynchronize(c->stream));  // the stream may still read the old one
-    c->dfree(c->partials);
-    c->bytes -= (size_t)c->nblocks_cap * lbm::MON_SLOTS * sizeof(double);
-    c->partials = grown;
-    c->nblocks_cap = nb;
-  }
   if (c->bx != t->bx || c->by != t->by || c->variant != t->variant) {
     HIP_TRY(hipStreamSynchronize(c->stream));  // a replay may still be in flight
     c->drop_graphs();
@@ -1491,7 +1472,6 @@ int lbm_set_tuning(lbm_ctx *c, const lbm_tuning *t) {
   c->bx = t->bx;
   c->by = t->by;
   c->variant = t->variant;
-  c->nblocks = nb;
   return LBM_OK;
 }
 
