@@ -126,8 +126,9 @@ __global__ void __launch_bounds__(256)
     const int node = (z * dm.ny + y) * dm.nx + x;
     T g[3];
     batch_force<T>(gbuf, dm, x, y, z, node, L::D, g);
-    const bool fast = tile_fast<S>(tile, dm, geo);
-    step_node<L, COLL, S, T, MEM>(fin + dm.base, fout + dm.base, geo, x, y, z, 0u, fast, g,
+    const bool small = (uint64_t)L::Q * dm.nz * dm.ps * sizeof(S) < (1ull << 32);
+    const int addr = tile_fast<S>(tile, dm, geo) ? ADDR_FAST : (small ? ADDR_SMALL : ADDR_WIDE);
+    step_node<L, COLL, S, T, MEM>(fin + dm.base, fout + dm.base, geo, x, y, z, 0u, addr, g,
                                   shift, T(dm.c0), T(dm.c1));
   }
 }

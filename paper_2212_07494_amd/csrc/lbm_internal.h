@@ -52,6 +52,7 @@ struct LaunchDesc {
   int variant;       // memory-access variant of the step kernel (MEM_*)
   int fast_ok;       // 1: blocks that cannot bounce back may take the scalar-base path
   int xcd;           // 1: XCD-contiguous block placement, 0: dispatch order
+  int linear;        // 1: the step's blocks take consecutive nodes of a layer, 0: tiles of rows
   // Dynamic LDS a workgroup of the step kernel reserves and never touches (0: none): it
   // caps the workgroups resident on a CU, and so the waves per SIMD, below what the
   // kernel's registers allow.

@@ -10,7 +10,7 @@
 // wavefront moves 64 consecutive values per plane in each direction.
 //
 // A thread owns one node.  Blocks tile (x, y) rows with blockDim = (bx, by), one z
-// slice per blockIdx.z.  Each node is read and written once per step and no value is
+// slice per blockIdx.z, or (linear blocks) take bx by consecutive nodes of a layer.  Each node is read and written once per step and no value is
 // reused by another block, so the block order carries no cache locality to exploit.
 #pragma once
 
@@ -150,6 +150,45 @@ __device__ __forceinline__ const S *pull_ptr_periodic(const S *f, int x, int y, 
   return at_offset(plane_ptr<L>(f, i, zs, G), (uint32_t)(ys * G.nx + xs));
 }
 
+// The same pull as a byte offset from the start of the buffer, for buffers under 4 GiB
+// (StepArgs::small): the layer and plane are uniform, so a population costs an addition to the
+// node's offset in the plane, and bounce-back a selection between two offsets.
+template <class L, class S>
+__device__ __forceinline__ uint32_t plane_off(int i, int z, const Geom &G) {
+  return (uint32_t)((uint64_t)(z * L::Q + i) * (uint64_t)G.ps * sizeof(S));
+}
+template <class L, int i, class S>
+__device__ __forceinline__ uint32_t pull_off(int x, int y, int z, const Geom &G, uint32_t sm) {
+  constexpr int ex = L::E[i][0], ey = L::E[i][1], ez = L::E[i][2];
+  int xs = x - ex, ys = y - ey, zs = z - ez;
+  bool bounce = false;
+  if constexpr (i < 31) bounce = (sm >> i) & 1u;  // the source node is solid
+  if constexpr (ex != 0) {
+    const bool o = (xs < 0) | (xs >= G.nx);
+    bounce |= o & (G.wall[0] != 0);
+    xs = (xs < 0) ? xs + G.nx : ((xs >= G.nx) ? xs - G.nx : xs);
+  }
+  if constexpr (ey != 0) {
+    const bool o = (ys < 0) | (ys >= G.ny);
+    bounce |= o & (G.wall[1] != 0);
+    ys = (ys < 0) ? ys + G.ny : ((ys >= G.ny) ? ys - G.ny : ys);
+  }
+  if constexpr (ez != 0) {
+    const bool o = (zs < 0) | (zs >= G.nz);
+    bounce |= o & (G.wall[2] != 0);
+    zs = (zs < 0) ? zs + G.nz : ((zs >= G.nz) ? zs - G.nz : zs);
+  }
+  const uint32_t from = plane_off<L, S>(i, zs, G) + (uint32_t)(ys * G.nx + xs) * (uint32_t)sizeof(S);
+  const uint32_t own =
+      plane_off<L, S>(L::OPP[i], z, G) + (uint32_t)(y * G.nx + x) * (uint32_t)sizeof(S);
+  return bounce ? own : from;
+}
+template <class S>
+__device__ __forceinline__ S *at_byte(S *f, uint32_t o) {
+  using B = std::conditional_t<std::is_const_v<S>, const char, char>;
+  return reinterpret_cast<S *>(reinterpret_cast<B *>(f) + o);
+}
+
 // Slot that node (x, y, z) pulls population i from: (i, x - e_i) with periodic wrap,
 // or (opp(i), x) when x - e_i crosses a wall face or is a solid node (halfway
 // bounce-back); sm is the node's solid mask word.
@@ -201,6 +240,11 @@ struct StepArgs {
   T c3;      // RMRT: h3; SMRT: (q_bulk - q2)/D (0 = one rate at order 2)
   T c4;      // SMRT: (q_31 - q3)/2 (0 = one rate at order 3)
   int fast_ok;  // 1: fast_block workgroups take the scalar-base path
+  int small;    // 1: a buffer's byte offsets fit 32 bits
+  // Linear blocks: 1, and the multiplier and shift of the division by nx (linear_row).
+  int linear;
+  uint32_t div_m;
+  int div_s;
   int xcd;      // 1: XCD-contiguous block placement (xcd_block), 0: dispatch order
 };
 
@@ -229,15 +273,30 @@ __device__ __forceinline__ void collide_node(T (&d)[L::Q], T shift, const T (&g)
   }
 }
 
+// n / nx for n < 2^31 by multiplication: m = ceil(2^(31 + s) / nx) < 2^32 with 2^(s-1) < nx <=
+// 2^s; n (m nx - 2^(31 + s)) < 2^31 2^s, so the quotient is exact.  m = 0 stands for nx = 1.
+__device__ __forceinline__ int linear_row(uint32_t n, uint32_t m, int s) {
+  return m ? (int)(__umulhi(n, m) >> (s - 1)) : (int)n;
+}
+
+// How a node's slots are addressed: ADDR_FAST where no pull of its block can bounce back
+// (scalar plane bases), ADDR_SMALL (32-bit byte offsets), ADDR_WIDE (64-bit addresses).
+enum { ADDR_WIDE = 0, ADDR_SMALL = 1, ADDR_FAST = 2 };
+
 // One node of the fused step: pull the populations (periodic wrap or halfway
 // bounce-back), collide with the force, store at the node's own slots.
 template <class L, int COLL, class S, class T, int MEM>
 __device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restrict__ fout,
                                           const Geom &geo, int x, int y, int z,
-                                          uint32_t sm, bool fast, const T (&g)[3], T shift,
+                                          uint32_t sm, int addr, const T (&g)[3], T shift,
                                           T c0, T c1, T c2 = T(0), T c3 = T(0), T c4 = T(0)) {
   T d[L::Q];
-  if (fast) {
+  if (addr == ADDR_SMALL) {
+    static_for<L::Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      d[i] = load_v<MEM, S, T>(at_byte(fin, pull_off<L, i, S>(x, y, z, geo, sm)));
+    });
+  } else if (addr == ADDR_FAST) {
     static_for<L::Q>([&](auto I) {
       constexpr int i = decltype(I)::value;
       d[i] = load_v<MEM, S, T>(pull_ptr_periodic<L, i>(fin, x, y, z, geo));
@@ -249,7 +308,13 @@ __device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restri
     });
   }
   collide_node<L, COLL>(d, shift, g, c0, c1, c2, c3, c4);
-  if (fast) {
+  if (addr == ADDR_SMALL) {
+    const uint32_t o = (uint32_t)(y * geo.nx + x) * (uint32_t)sizeof(S);
+    static_for<L::Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      store_v<MEM, S, T>(at_byte(fout, plane_off<L, S>(i, z, geo) + o), d[i]);
+    });
+  } else if (addr == ADDR_FAST) {
     const uint32_t o = (uint32_t)(y * geo.nx + x);
     static_for<L::Q>([&](auto I) {
       constexpr int i = decltype(I)::value;
@@ -275,20 +340,37 @@ __global__ void __launch_bounds__(256) step_kernel(StepArgs<T> a) {
     byi = (int)((t % nxy) / gridDim.x);
     bxi = (int)(t % gridDim.x);
   }
-  const int x = bxi * blockDim.x + threadIdx.x;
-  const int y = byi * blockDim.y + threadIdx.y;
+  int x, y;
   const int z = bzi;
-  if (x >= a.geo.nx || y >= a.geo.ny) return;
+  int x0, x1, y0, y1;  // the block's extent
+  if (a.linear) {
+    const uint32_t n0 = (uint32_t)bxi * (blockDim.x * blockDim.y);
+    const uint32_t n = n0 + threadIdx.y * blockDim.x + threadIdx.x;
+    const uint32_t nl = min(n0 + blockDim.x * blockDim.y, (uint32_t)(a.geo.nx * a.geo.ny)) - 1;
+    if (n > nl) return;
+    y = linear_row(n, a.div_m, a.div_s);
+    x = (int)n - y * a.geo.nx;
+    x0 = 0;
+    x1 = a.geo.nx - 1;
+    y0 = linear_row(n0, a.div_m, a.div_s);
+    y1 = linear_row(nl, a.div_m, a.div_s);
+  } else {
+    x0 = bxi * blockDim.x;
+    y0 = byi * blockDim.y;
+    x1 = x0 + (int)blockDim.x - 1;
+    y1 = y0 + (int)blockDim.y - 1;
+    x = x0 + threadIdx.x;
+    y = y0 + threadIdx.y;
+    if (x >= a.geo.nx || y >= a.geo.ny) return;
+  }
   const int node = (z * a.geo.ny + y) * a.geo.nx + x;
   const uint32_t sm = node_mask(a.geo, node);
   if (sm & SOLID_NODE) return;  // no fluid here: nothing pulls from its slots
   T g[3];
   load_force<T, GK>(a.force, x, y, z, node, a.geo.N, L::D, g);
-  const int x0 = bxi * blockDim.x, y0 = byi * blockDim.y;
-  const bool fast = a.fast_ok && fast_block<S>(a.geo, x0, x0 + (int)blockDim.x - 1, y0,
-                                               y0 + (int)blockDim.y - 1, z);
+  const int addr = a.fast_ok && fast_block<S>(a.geo, x0, x1, y0, y1, z) ? ADDR_FAST : a.small;
   step_node<L, COLL, S, T, MEM>(static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.geo,
-                                x, y, z, sm, fast, g, a.shift, a.c0, a.c1, a.c2, a.c3,
+                                x, y, z, sm, addr, g, a.shift, a.c0, a.c1, a.c2, a.c3,
                                 a.c4);
 }
 

@@ -37,6 +37,14 @@ inline StepArgs<T> make_args(const LaunchDesc &d) {
   a.c3 = T(d.c3);
   a.c4 = T(d.c4);
   a.fast_ok = d.fast_ok;
+  a.small = 0;
+  a.linear = d.linear;
+  a.div_m = 0;
+  a.div_s = 0;
+  if (d.geo.nx > 1) {
+    while ((1u << a.div_s) < (uint32_t)d.geo.nx) ++a.div_s;
+    a.div_m = (uint32_t)(((1ull << (31 + a.div_s)) + d.geo.nx - 1) / d.geo.nx);
+  }
   a.xcd = d.xcd;
   return a;
 }
@@ -69,8 +77,12 @@ template <class L>
 struct Ops {
   template <int COLL, class S, class T, int GK, int MEM>
   static hipError_t step_m(const LaunchDesc &d, hipStream_t s) {
-    hipLaunchKernelGGL((step_kernel<L, COLL, S, T, GK, MEM>), grid_of(d), dim3(d.bx, d.by),
-                       d.lds_pad, s, make_args<T>(d));
+    StepArgs<T> a = make_args<T>(d);
+    a.small = (uint64_t)L::Q * d.geo.nz * d.geo.ps * sizeof(S) < (1ull << 32);
+    const unsigned nb = (unsigned)(((int64_t)d.geo.nx * d.geo.ny + d.bx * d.by - 1) / (d.bx * d.by));
+    const dim3 grid = d.linear ? dim3(nb, 1, d.geo.nz) : grid_of(d);
+    hipLaunchKernelGGL((step_kernel<L, COLL, S, T, GK, MEM>), grid, dim3(d.bx, d.by), d.lds_pad, s,
+                       a);
     return hipGetLastError();
   }
   template <int COLL, class S, class T, int GK>

@@ -102,6 +102,16 @@ bool shifted(int s) { return s == LBM_F32_SHIFTED || s == LBM_F16_SHIFTED; }
 
 using lbm::ops_for;
 
+// Launch variant before any tuning, by the bytes of the two population buffers: while they
+// fit the 256 MB last-level cache, or nearly, plain accesses (the next step reads what this one
+// writes) and blocks placed XCD by XCD; beyond it non-temporal stores, in dispatch order.
+// Both on the scalar-base path.  Measured (us per step: general plain / 9 / 4): D3Q19
+// FP32-shifted 80^3 (78 MB) 17.0 / 15.3 / 18.5, 112^3 (214 MB) 39.0 / 37.5 / 41.3, 128^3
+// (319 MB) 60.7 / 54.7 / 58.0, 150^3 (513 MB) 110.8 / 107.0 / 105.5; D3Q27 FP64 84^3 (256 MB)
+// 53.2 / 45.3 / 50.8, 96^3 (382 MB) 83.0 / 78.3 / 72.6, 128^3 (1.8 GB) 171 / - / 166.
+constexpr size_t kCachedBytes = 320u << 20;
+int default_variant(size_t pop_bytes) { return 2 * pop_bytes <= kCachedBytes ? 9 : 4; }
+
 // Block shape: 64-wide rows (one wavefront per row segment), up to 256 threads.
 void block_shape(int nx, int &bx, int &by) {
   bx = nx >= 256 ? 256 : (nx >= 128 ? 128 : 64);
@@ -286,6 +296,11 @@ struct lbm_ctx {
     d.variant = base % kMemVariants;
     d.fast_ok = (base / kMemVariants) % 2;
     d.xcd = base / (2 * kMemVariants);
+    // rows that fill no wavefront leave its last lanes idle, and as many memory requests
+    // for them; consecutive nodes of the layer fill them all (D3Q19 BGK FP64 131 x 67 x 59
+    // with walls: 39.7 -> 31.5 us a step as launched by default then, 160^3 FP64 267 -> 215;
+    // 100^3 FP32-shifted 35.4 -> 29.9)
+    d.linear = p.nx % 64 != 0;
     d.lds_pad = lds_for_cap(kWaveCaps[variant / kBaseVariants], bx, by, lds_cu, lds_block);
     return d;
   }
@@ -784,6 +799,7 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
     c->multi = lbm::multi_plan(p->nx, p->ny, p->bc[1] == LBM_WALLS, storage_bytes(p->storage),
                                c->lds_cu, ncu);
   const size_t pop_bytes = (size_t)c->Q * (size_t)c->N * storage_bytes(p->storage);
+  c->variant = default_variant(pop_bytes);
   const size_t ab = arith_bytes(p->storage);
   // force table, in the arithmetic type
   std::vector<double> gh;
