@@ -328,7 +328,10 @@ __device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restri
   }
 }
 
-template <class L, int COLL, class S, class T, int GK, int MEM>
+// PLAIN: a lattice without walls or solid nodes whose rows fill wavefronts; the kernel then
+// holds neither linear blocks nor 32-bit offsets with bounce-back, which cost such lattices 1%
+// (D3Q27 FP32-shifted 128^3: 76.9 against 78.0 us a step, D3Q19 256^3 408 against 412).
+template <class L, int COLL, class S, class T, int GK, int MEM, bool PLAIN>
 __global__ void __launch_bounds__(256) step_kernel(StepArgs<T> a) {
   // the block's place in the lattice (uniform across the workgroup)
   int bxi = blockIdx.x, byi = blockIdx.y, bzi = blockIdx.z;
@@ -343,7 +346,7 @@ __global__ void __launch_bounds__(256) step_kernel(StepArgs<T> a) {
   int x, y;
   const int z = bzi;
   int x0, x1, y0, y1;  // the block's extent
-  if (a.linear) {
+  if (!PLAIN && a.linear) {
     const uint32_t n0 = (uint32_t)bxi * (blockDim.x * blockDim.y);
     const uint32_t n = n0 + threadIdx.y * blockDim.x + threadIdx.x;
     const uint32_t nl = min(n0 + blockDim.x * blockDim.y, (uint32_t)(a.geo.nx * a.geo.ny)) - 1;
@@ -368,7 +371,7 @@ __global__ void __launch_bounds__(256) step_kernel(StepArgs<T> a) {
   if (sm & SOLID_NODE) return;  // no fluid here: nothing pulls from its slots
   T g[3];
   load_force<T, GK>(a.force, x, y, z, node, a.geo.N, L::D, g);
-  const int addr = a.fast_ok && fast_block<S>(a.geo, x0, x1, y0, y1, z) ? ADDR_FAST : a.small;
+  const int addr = a.fast_ok && fast_block<S>(a.geo, x0, x1, y0, y1, z) ? ADDR_FAST : (PLAIN ? ADDR_WIDE : a.small);
   step_node<L, COLL, S, T, MEM>(static_cast<const S *>(a.fin), static_cast<S *>(a.fout), a.geo,
                                 x, y, z, sm, addr, g, a.shift, a.c0, a.c1, a.c2, a.c3,
                                 a.c4);
