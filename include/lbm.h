@@ -196,11 +196,11 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init,
 
 /* Advance n >= 0 steps.  g_scale: NULL (s(t) = 1) or n host doubles, the factor s(t)
  * of g(x) for each step.  Enqueues work only (no synchronisation), except as below.
- * D2Q9: up to five steps are taken by one launch (tiles that recompute their margins), except
+ * D2Q9: up to five steps (seven on small lattices) are taken by one launch (tiles that recompute their margins), except
  * with debug_poison or where a periodic lattice has fewer than three rows; the launch
  * configuration (lbm_tuning) is that of the single steps that remain.
  * Small lattices (N <= 2^21 nodes), where launch overhead dominates: when n covers at
- * least two chunks of 64 steps (70 with five steps a launch, 66 with three) and neither
+ * least two chunks of 64 steps (70 with five or seven steps a launch, 66 with three) and neither
  * monitor_every nor debug_poison is set, the chunks are replayed from a HIP graph captured
  * once per buffer parity (the factors s(t)
  * are then staged in pinned host memory, uploaded asynchronously and read on the device;

@@ -26,17 +26,16 @@ hipError_t launch(const LaunchDesc &d, const MultiPlan &p, int k, const double *
   D.c3 = T(d.c3);
   D.c4 = T(d.c4);
   MultiScale<T> sc;
-  for (int j = 0; j < MULTI_STEPS; ++j) sc.v[j] = T(gs && j < k ? gs[j] : d.gscale);
+  for (int j = 0; j < MULTI_STEPS_MAX; ++j) sc.v[j] = T(gs && j < k ? gs[j] : d.gscale);
   sc.sdev = d.gs_dev;
   sc.sctr = d.gs_ctr;
   sc.sj = d.gs_j;
   const dim3 grid(p.ntx * p.nty), block(MULTI_THREADS);
-  if (d.gk)
-    hipLaunchKernelGGL((multi_step_kernel<D2Q9, COLL, S, T, true>), grid, block, p.lds, s, D, sc,
-                       k, p.ox, p.oy, p.ntx);
-  else
-    hipLaunchKernelGGL((multi_step_kernel<D2Q9, COLL, S, T, false>), grid, block, p.lds, s, D, sc,
-                       k, p.ox, p.oy, p.ntx);
+  const auto kernel = p.wx == 32 ? (d.gk ? multi_step_kernel<D2Q9, COLL, S, T, 32, true>
+                                         : multi_step_kernel<D2Q9, COLL, S, T, 32, false>)
+                                 : (d.gk ? multi_step_kernel<D2Q9, COLL, S, T, 64, true>
+                                         : multi_step_kernel<D2Q9, COLL, S, T, 64, false>);
+  hipLaunchKernelGGL(kernel, grid, block, p.lds, s, D, sc, k, p.ox, p.oy, p.ntx);
   return hipGetLastError();
 }
 
@@ -70,24 +69,54 @@ hipError_t by_collision(const BatchLaunch &b, int k, hipStream_t s) {
 
 }  // namespace
 
+// Steps, columns and rows of the tiles.  A launch whose tiles each find a compute unit of
+// their own lasts as long as one tile, whose stages take their rows in passes of the
+// workgroup's wavefronts: about six rows' worth of latency a pass besides the rows themselves,
+// after 22 for the launch.  There rows of 32 columns, two to a wavefront, halve the passes, and
+// the idle units pay for the wider margins (us a step, 64 against 32 columns: 64 x 32 BGK FP64
+// 1.80 / 1.58, 50 x 200 SMRT FP64 1.61 / 1.47, 128^2 FP64 1.57 / 1.46, 256^2 FP64 2.07 / 1.94);
+// and more steps a launch, where their rows still make one pass.  Launches with more tiles than
+// units are bound by the rows (multi_cost).
 MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu) {
   MultiPlan p{};
-  const int K = multi_steps(ny, wy);
   // a plane's byte offsets are 32-bit in the kernel
-  if (!K || ncu < 1 || (uint64_t)nx * ny * elem >= (1ull << 32)) return p;
-  p.ntx = multi_columns(nx, K);
-  p.ox = (nx + p.ntx - 1) / p.ntx;
+  if (ncu < 1 || (uint64_t)nx * ny * elem >= (1ull << 32)) return p;
+  constexpr int WAVES = MULTI_THREADS / 64;
+  const int few = multi_steps(ny, wy);
   double best = 0;
-  for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem) <= (size_t)lds_cu; ++oy) {
-    const int nty = (ny + oy - 1) / oy;
-    const double cost = multi_cost((int64_t)p.ntx * nty, oy, K, ncu);
-    if (p.K && cost >= best) continue;
-    best = cost;
-    p.K = K;
-    p.oy = oy;
-    p.nty = nty;
+  auto consider = [&](int K, int wx, bool single) {
+    const int rpw = 64 / wx, ntx = multi_columns(nx, K, wx);
+    for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem, wx) <= (size_t)lds_cu; ++oy) {
+      const int nty = (ny + oy - 1) / oy;
+      const int64_t tiles = (int64_t)ntx * nty;
+      if (single != (tiles <= ncu)) continue;
+      double cost = multi_cost(tiles, oy, K, ncu);
+      if (single) {
+        cost = 22;
+        for (int s = 0; s < K; ++s) {
+          const int rows = (oy + 2 * s + rpw - 1) / rpw;  // of the last stage first
+          cost += 6 * ((rows + WAVES - 1) / WAVES) + rows;
+        }
+        cost /= K;
+      }
+      if (p.K && cost >= best) continue;
+      best = cost;
+      p.K = K;
+      p.wx = wx;
+      p.ntx = ntx;
+      p.oy = oy;
+      p.nty = nty;
+    }
+  };
+  if (few) {
+    consider(few, MULTI_W, true);
+    consider(few, 32, true);
+    if (wy || ny >= 2 * MULTI_STEPS_MAX) consider(MULTI_STEPS_MAX, 32, true);
+    if (!p.K) consider(few, MULTI_W, false);
   }
-  p.lds = (unsigned)multi_lds(p.oy, K, elem);
+  if (!p.K) return p;
+  p.ox = (nx + p.ntx - 1) / p.ntx;
+  p.lds = (unsigned)multi_lds(p.oy, p.K, elem, p.wx);
   return p;
 }
 

@@ -65,9 +65,10 @@ struct LaunchDesc {
 };
 
 // Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
-// tile, steps of a launch, threads of a workgroup, and the most rows a plan lets a tile own.
+// tile, steps of a launch (and of one on the smallest lattices), threads of a workgroup, and
+// the most rows a plan lets a tile own.
 constexpr int MULTI_W = 64;
-constexpr int MULTI_STEPS = 5;
+constexpr int MULTI_STEPS = 5, MULTI_STEPS_MAX = 7;
 constexpr int MULTI_THREADS = 512;
 constexpr int MULTI_ROWS = 27;
 
@@ -75,21 +76,21 @@ constexpr int MULTI_ROWS = 27;
 // steps (odd, at least 3; 0: no such plan), tiles of ox x oy nodes in an ntx x nty grid,
 // workgroups with `lds` bytes of LDS.
 struct MultiPlan {
-  int K, ox, oy, ntx, nty;
+  int K, wx, ox, oy, ntx, nty;  // wx: columns of a wavefront's row (64 or 32)
   unsigned lds;
 };
 
 // The tiles a lattice's nx columns are split into, one beside the other, for K steps a
-// launch: one of up to 64 columns that wraps (or bounces) inside itself, else tiles that
+// launch: one of up to wx columns that wraps (or bounces) inside itself, else tiles that
 // leave room for K - 1 columns more on each side.
-inline int multi_columns(int nx, int K) {
-  const int room = nx <= MULTI_W ? nx : MULTI_W - 2 * (K - 1);
+inline int multi_columns(int nx, int K, int wx = MULTI_W) {
+  const int room = nx <= wx ? nx : wx - 2 * (K - 1);
   return (nx + room - 1) / room;
 }
 // LDS of a tile of oy rows, and the steps of a launch on a lattice of ny rows (0: none; a
 // periodic lattice wraps once, and one of few rows would mostly compute its margins).
-inline size_t multi_lds(int oy, int K, size_t elem) {
-  return (size_t)(oy + 2 * (K - 1)) * MULTI_W * 9 * elem;
+inline size_t multi_lds(int oy, int K, size_t elem, int wx = MULTI_W) {
+  return (size_t)(oy + 2 * (K - 1)) * wx * 9 * elem;
 }
 inline int multi_steps(int ny, bool wy) { return wy || ny >= 12 ? MULTI_STEPS : (ny >= 3 ? 3 : 0); }
 // Relative time of a launch of `tiles` tiles of oy rows: the compute units take them in

@@ -7,13 +7,13 @@
 // writes the tile back.  Every node value is the one the single-step kernel computes, in the
 // same operations; the nodes of the widened tile are computed more than once.
 //
-// Layout.  A wavefront works on one row of up to 64 nodes, x = x0 - hx + lane; the rows of a
-// stage are dealt to the workgroup's wavefronts in turn.  Row and plane addresses are then
+// Layout.  A wavefront works on one row of up to WX = 64 nodes, x = x0 - hx + lane; the rows of
+// a stage are dealt to the workgroup's wavefronts in turn.  Row and plane addresses are then
 // uniform (scalar), and a lane holds three column offsets (its own and its neighbours') for
-// the whole launch.  A lattice of at most 64 columns is one tile wide and wraps (or bounces)
-// inside it: no widening in x.  LDS holds slot (row, i, x) at (row Q + i) 64 + x, so all of a
+// the whole launch.  A lattice of at most WX columns is one tile wide and wraps (or bounces)
+// inside it: no widening in x.  LDS holds slot (row, i, x) at (row Q + i) WX + x, so all of a
 // node's slots are at constant distances from its own and a row of lanes is free of bank
-// conflicts.
+// conflicts.  WX = 32 puts two rows into a wavefront (multi_plan says when).
 //
 // One copy of the populations in LDS is enough.  Slot (i, y) in the kernel's usual meaning
 // ("own": the post-collision population i of node y) is read by node y + e_i alone.  A node
@@ -29,16 +29,19 @@
 // launch; on the lattices that fit the caches the launch and the latency of its loads are all
 // there is to a step (3 us at 64 x 32).  Five steps a launch share one launch and one pass
 // over memory, and the vector ALU becomes the bound: about 240 instructions a node and stage,
-// twice the bare arithmetic of the widened tile's nodes.  Measured, us per step, single steps
-// against five a launch: 64 x 32 BGK FP64 3.1 / 1.9; 50 x 200 SMRT FP64 3.2 / 1.7; 512^2 FP64
-// 9.4 / 4.3; 1024^2 SMRT FP32-shifted 13.4 / 8.1, FP64 24.9 / 13.6; 2048^2 FP32-shifted 57 /
-// 26; a batch of 512 domains (5.8 million nodes) FP32-shifted 120 / 52.
+// twice the bare arithmetic of the widened tile's nodes.  With one or two wavefronts a SIMD,
+// as on the smallest lattices, an instruction takes about eight cycles instead of four, and a
+// stage's chain of them (1,400 to 2,500 cycles) is the floor.  Measured, us per step, single
+// steps against these launches: 64 x 32 BGK FP64 3.1 / 1.55; 50 x 200 SMRT FP64 3.2 / 1.45;
+// 512^2 FP64 9.4 / 4.3; 1024^2 SMRT FP32-shifted 13.4 / 8.1, FP64 24.9 / 13.6; 2048^2
+// FP32-shifted 57 / 26; a batch of 512 domains (5.8 million nodes) FP32-shifted 120 / 52.
 //
-// Why five.  Three and seven steps a launch were slower at every size tried (128^2: 1.57 and
-// 1.95 against 1.37; 900^2 FP32-shifted: 6.2 and 8.2 against 6.1): fewer leave more of the
-// launch, more widen the tile.  512 threads: more wavefronts than a stage has rows idle, and
-// two workgroups of eight wavefronts hide each other's barriers (1024 threads: 10.3 against
-// 8.1 at 1024^2).
+// Why five.  Three and seven steps a launch of 64-column tiles were slower at every size tried
+// (128^2: 1.57 and 1.95 against 1.37; 900^2 FP32-shifted: 6.2 and 8.2 against 6.1): fewer leave
+// more of the launch, more widen the tile.  Seven pay on 32-column tiles while their rows
+// make one pass of the wavefronts (32^2 FP64 1.27 against 1.35).  512 threads: more wavefronts
+// than a stage has rows idle, and two workgroups of eight wavefronts hide each other's
+// barriers (1024 threads: 10.3 against 8.1 at 1024^2).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -73,7 +76,7 @@ struct MultiTile {
 // Force factors of the launch's steps: one value, or from device memory (graph replays).
 template <class T>
 struct MultiScale {
-  T v[MULTI_STEPS];
+  T v[MULTI_STEPS_MAX];
   const double *sdev;  // sdev[*sctr + sj + s] if set
   const int64_t *sctr;
   int sj;
@@ -88,32 +91,35 @@ using LdsPtr = __attribute__((address_space(3))) S *;
 struct MultiFrame {
   int hx, hy, ex, ey;  // margins below the owned nodes, extents
   int gx, gl, gr;      // this lane's lattice column and its neighbours'
-  int cl, cr;          // the neighbours' columns in the tile
+  int col, cl, cr;     // its and the neighbours' columns in the tile
   bool at_l, at_r;     // a wall beside this column
   int wave, nwaves, lane;
+  int sub;             // its row among the wavefront's
 };
 
-template <class T>
+template <int WX, class T>
 __device__ __forceinline__ MultiFrame multi_frame(const MultiDom<T> &D, const MultiTile &tile,
                                                   int H) {
   MultiFrame f;
   f.lane = threadIdx.x & 63;
+  f.col = f.lane % WX;
+  f.sub = f.lane / WX;
   f.wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   f.nwaves = blockDim.x >> 6;
-  const bool whole = D.nx <= MULTI_W;  // one tile wide: wraps or bounces inside the tile
+  const bool whole = D.nx <= WX;  // one tile wide: wraps or bounces inside the tile
   const int room_l = D.wx ? min(H, tile.x0) : H;
   const int room_r = D.wx ? min(H, D.nx - tile.x0 - tile.ox) : H;
   f.hx = whole ? 0 : room_l;
   f.ex = f.hx + tile.ox + (whole ? 0 : room_r);
   f.hy = D.wy ? min(H, tile.y0) : H;
   f.ey = f.hy + tile.oy + (D.wy ? min(H, D.ny - tile.y0 - tile.oy) : H);
-  int gx = tile.x0 - f.hx + f.lane;
+  int gx = tile.x0 - f.hx + f.col;
   gx = gx < 0 ? gx + D.nx : (gx >= D.nx ? gx - D.nx : gx);
   f.gx = gx;
   f.gl = gx == 0 ? D.nx - 1 : gx - 1;
   f.gr = gx == D.nx - 1 ? 0 : gx + 1;
-  f.cl = whole && f.lane == 0 ? D.nx - 1 : f.lane - 1;
-  f.cr = whole && f.lane == D.nx - 1 ? 0 : f.lane + 1;
+  f.cl = whole && f.col == 0 ? D.nx - 1 : f.col - 1;
+  f.cr = whole && f.col == D.nx - 1 ? 0 : f.col + 1;
   f.at_l = D.wx && gx == 0;
   f.at_r = D.wx && gx == D.nx - 1;
   return f;
@@ -159,26 +165,30 @@ enum { ST_FIRST = 0, ST_PULL = 1, ST_SWAP = 2, ST_LAST = 3 };
 
 // Stage s of the tile.  BOUNCE: some node of the widened tile may bounce back (walls or
 // solid nodes).
-template <class L, int COLL, class S, class T, bool BOUNCE, bool FIELD, int STAGE>
+template <class L, int COLL, class S, class T, int WX, bool BOUNCE, bool FIELD, int STAGE>
 __device__ __forceinline__ void multi_stage(const MultiDom<T> &D, const MultiTile &tile,
                                             const MultiFrame &f, const MultiForce<T> &F, int m,
                                             T sc, LdsPtr<S> lds) {
   static_assert(L::D == 2);
   constexpr int Q = L::Q;
-  constexpr int ROW = Q * MULTI_W;  // LDS elements of a row
+  constexpr int ROW = Q * WX;    // LDS elements of a row
+  constexpr int RPW = 64 / WX;   // rows of a wavefront
   const S *__restrict__ fin = static_cast<const S *>(D.fin);
   S *__restrict__ fout = static_cast<S *>(D.fout);
   const int nx = D.nx, ny = D.ny;
   const int xlo = max(0, f.hx - m), xhi = min(f.ex, f.hx + tile.ox + m);
   const int ylo = max(0, f.hy - m), yhi = min(f.ey, f.hy + tile.oy + m);
-  const bool live = f.lane >= xlo && f.lane < xhi;
-  for (int r = ylo + f.wave; r < yhi; r += f.nwaves) {
+  const bool in_x = f.col >= xlo && f.col < xhi;
+  for (int rb = ylo + f.wave * RPW; rb < yhi; rb += f.nwaves * RPW) {
+    const int r = RPW == 1 ? rb : rb + f.sub;  // uniform where a wavefront has one row
+    const bool live = in_x && (RPW == 1 || r < yhi);
     int gy = tile.y0 - f.hy + r;
     gy = gy < 0 ? gy + ny : (gy >= ny ? gy - ny : gy);
     const int row = gy * nx;
     T g[3] = {F.lane[0], F.lane[1], T(0)};
     if (!FIELD && F.by_row)  // with every lane of the wavefront active
-      for (int a = 0; a < 2; ++a) g[a] = lane_value(F.lane[a], r);
+      for (int a = 0; a < 2; ++a)
+        g[a] = RPW == 1 ? lane_value(F.lane[a], r) : __shfl(F.lane[a], r, 64);
     if (!live) continue;
     uint32_t sm = 0;
     if constexpr (BOUNCE) {
@@ -201,14 +211,14 @@ __device__ __forceinline__ void multi_stage(const MultiDom<T> &D, const MultiTil
       for (int a = 0; a < 2; ++a) g[a] = *at_offset(D.tab + ((int64_t)a * D.n + row), f.gx);
     for (int a = 0; a < 2; ++a) g[a] = g[a] * sc;
     const LdsPtr<S> lrow = lds + r * ROW;
-    const LdsPtr<S> own = lrow + f.lane, left = lrow + f.cl, right = lrow + f.cr;
+    const LdsPtr<S> own = lrow + f.col, left = lrow + f.cl, right = lrow + f.cr;
     // the slot population i is pulled from
     auto source = [&](auto I) -> LdsPtr<S> {
       constexpr int i = decltype(I)::value;
       constexpr int ex = L::E[i][0], ey = L::E[i][1];
-      LdsPtr<S> p = (ex > 0 ? left : (ex < 0 ? right : own)) + (i * MULTI_W - ey * ROW);
+      LdsPtr<S> p = (ex > 0 ? left : (ex < 0 ? right : own)) + (i * WX - ey * ROW);
       if constexpr (BOUNCE && i > 0)
-        if (bounces(I)) p = own + L::OPP[i] * MULTI_W;
+        if (bounces(I)) p = own + L::OPP[i] * WX;
       return p;
     };
     T d[Q];
@@ -234,7 +244,7 @@ __device__ __forceinline__ void multi_stage(const MultiDom<T> &D, const MultiTil
     } else {
       static_for<Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        d[i] = T(own[L::OPP[i] * MULTI_W]);
+        d[i] = T(own[L::OPP[i] * WX]);
       });
     }
     collide_node<L, COLL>(d, D.shift, g, D.c0, D.c1, D.c2, D.c3, D.c4);
@@ -248,46 +258,46 @@ __device__ __forceinline__ void multi_stage(const MultiDom<T> &D, const MultiTil
     } else {
       static_for<Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        own[i * MULTI_W] = S(d[i]);
+        own[i * WX] = S(d[i]);
       });
     }
   }
 }
 
 // K steps of a tile (K odd, >= 3: the last stage then reads the swapped slots).
-template <class L, int COLL, class S, class T, bool BOUNCE, bool FIELD>
+template <class L, int COLL, class S, class T, int WX, bool BOUNCE, bool FIELD>
 __device__ __forceinline__ void multi_tile(const MultiDom<T> &D, const MultiTile &tile, int K,
                                            const MultiScale<T> &scale, LdsPtr<S> lds) {
   const int H = K - 1;
-  const MultiFrame f = multi_frame(D, tile, H);
+  const MultiFrame f = multi_frame<WX>(D, tile, H);
   const MultiForce<T> F = multi_force(D, tile, f, scale, K);
   auto factor = [&](int s) -> T { return lane_value(F.factor, s); };
-  multi_stage<L, COLL, S, T, BOUNCE, FIELD, ST_FIRST>(D, tile, f, F, H, factor(0), lds);
+  multi_stage<L, COLL, S, T, WX, BOUNCE, FIELD, ST_FIRST>(D, tile, f, F, H, factor(0), lds);
   __syncthreads();
   for (int s = 1;; s += 2) {
-    multi_stage<L, COLL, S, T, BOUNCE, FIELD, ST_PULL>(D, tile, f, F, H - s, factor(s), lds);
+    multi_stage<L, COLL, S, T, WX, BOUNCE, FIELD, ST_PULL>(D, tile, f, F, H - s, factor(s), lds);
     __syncthreads();
     if (s + 1 == H) break;
-    multi_stage<L, COLL, S, T, BOUNCE, FIELD, ST_SWAP>(D, tile, f, F, H - s - 1, factor(s + 1), lds);
+    multi_stage<L, COLL, S, T, WX, BOUNCE, FIELD, ST_SWAP>(D, tile, f, F, H - s - 1, factor(s + 1), lds);
     __syncthreads();
   }
-  multi_stage<L, COLL, S, T, BOUNCE, FIELD, ST_LAST>(D, tile, f, F, 0, factor(H), lds);
+  multi_stage<L, COLL, S, T, WX, BOUNCE, FIELD, ST_LAST>(D, tile, f, F, 0, factor(H), lds);
 }
 
 // Tile t with or without bounce-back, whichever its widened nodes need.
-template <class L, int COLL, class S, class T, bool FIELD>
+template <class L, int COLL, class S, class T, int WX, bool FIELD>
 __device__ __forceinline__ void multi_run(const MultiDom<T> &D, const MultiTile &t, int K,
                                           const MultiScale<T> &scale, unsigned char *lds_raw) {
   const bool bounce = D.smask || (D.wx && (t.x0 < K || t.x0 + t.ox > D.nx - K)) ||
                       (D.wy && (t.y0 < K || t.y0 + t.oy > D.ny - K));
   const LdsPtr<S> lds = (LdsPtr<S>)(lds_raw);
   if (bounce)
-    multi_tile<L, COLL, S, T, true, FIELD>(D, t, K, scale, lds);
+    multi_tile<L, COLL, S, T, WX, true, FIELD>(D, t, K, scale, lds);
   else
-    multi_tile<L, COLL, S, T, false, FIELD>(D, t, K, scale, lds);
+    multi_tile<L, COLL, S, T, WX, false, FIELD>(D, t, K, scale, lds);
 }
 
-template <class L, int COLL, class S, class T, bool FIELD>
+template <class L, int COLL, class S, class T, int WX, bool FIELD>
 __global__ void __launch_bounds__(MULTI_THREADS)
     multi_step_kernel(MultiDom<T> D, MultiScale<T> scale, int K, int ox, int oy, int ntx) {
   extern __shared__ __align__(16) unsigned char multi_lds_raw[];
@@ -298,7 +308,7 @@ __global__ void __launch_bounds__(MULTI_THREADS)
   t.y0 = ty * oy;
   t.ox = min(ox, D.nx - t.x0);
   t.oy = min(oy, D.ny - t.y0);
-  multi_run<L, COLL, S, T, FIELD>(D, t, K, scale, multi_lds_raw);
+  multi_run<L, COLL, S, T, WX, FIELD>(D, t, K, scale, multi_lds_raw);
 }
 
 // The same over the tiles of a batch: one workgroup a tile, none for inactive domains.
@@ -329,12 +339,12 @@ __global__ void __launch_bounds__(MULTI_THREADS)
   D.c1 = T(dm.c1);
   D.c2 = D.c3 = D.c4 = T(0);
   MultiScale<T> one{};
-  for (int s = 0; s < MULTI_STEPS; ++s) one.v[s] = T(1);
+  for (int s = 0; s < MULTI_STEPS_MAX; ++s) one.v[s] = T(1);
   const MultiTile t = {bt.x0, bt.y0, bt.ox, bt.oy};
   if (dm.gaxis == 3)
-    multi_run<L, COLL, S, T, true>(D, t, K, one, multi_lds_raw);
+    multi_run<L, COLL, S, T, MULTI_W, true>(D, t, K, one, multi_lds_raw);
   else
-    multi_run<L, COLL, S, T, false>(D, t, K, one, multi_lds_raw);
+    multi_run<L, COLL, S, T, MULTI_W, false>(D, t, K, one, multi_lds_raw);
 }
 
 }  // namespace lbm

@@ -53,6 +53,9 @@ CASES = [
     (130, 61, (1, 0, 0), "y", 5, "smrt", "f32s", {}),
     (129, 300, (1, 1, 0), "field", 5, "rmrt", "f64", {}),
     (300, 333, (0, 0, 0), "field", 6, "smrt", "f16s", {}),
+    (40, 14, (0, 0, 0), "field", 7, "smrt", "f64", {}),
+    (32, 33, (0, 1, 0), "y", 14, "bgk", "f64", {}),
+    (33, 3, (1, 1, 0), "x", 13, "smrt", "f32s", {}),
     (70, 37, (0, 0, 0), "y", 5, "smrt", "f64", dict(force_order=3)),
     (70, 37, (0, 1, 0), "y", 5, "smrt", "f32s", dict(force_order=4)),
     (70, 37, (0, 0, 0), "field", 5, "smrt", "f64", dict(tau_bulk=0.9)),
