@@ -13,9 +13,9 @@ constexpr int kUmax = MON_UMAX;
 
 // Sum the per-block partials in a fixed order: wavefront s takes slot s, lane l the blocks l,
 // l + 64, ... in turn, then a fixed tree combines the lanes.  The result is deterministic
-// for a given block count.
+// for a given block count.  host (or NULL): a second copy of the record, in pinned memory.
 __global__ void __launch_bounds__(64 * kSlots) finalize_kernel(const double *partials, int64_t nb,
-                                                               double *out) {
+                                                               double *out, double *host) {
   const int s = threadIdx.x >> 6, lane = threadIdx.x & 63;
   double acc = 0.0;
 #pragma unroll 8
@@ -27,7 +27,10 @@ __global__ void __launch_bounds__(64 * kSlots) finalize_kernel(const double *par
     const double t = __shfl_xor(acc, o, 64);
     acc = (s == kUmax) ? fmax(acc, t) : acc + t;
   }
-  if (lane == 0) out[s] = acc;
+  if (lane == 0) {
+    out[s] = acc;
+    if (host) host[s] = acc;
+  }
 }
 
 // Copy variants (16-byte vectors):
@@ -176,8 +179,9 @@ hipError_t fill_nan(void *p, size_t bytes, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t finalize_monitors(const double *partials, int64_t nb, double *out, hipStream_t s) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64 * kSlots), 0, s, partials, nb, out);
+hipError_t finalize_monitors(const double *partials, int64_t nb, double *out, double *host,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(64 * kSlots), 0, s, partials, nb, out, host);
   return hipGetLastError();
 }
 

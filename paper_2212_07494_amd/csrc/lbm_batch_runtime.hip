@@ -77,6 +77,7 @@ struct lbm_batch {
   double *partials = nullptr;
   int *active_d = nullptr, *n_active_d = nullptr;
   lbm::DomState *state_d = nullptr;
+  lbm::HostFields fields;  // small read-backs
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   size_t bytes = 0;
@@ -274,6 +275,7 @@ void release(lbm_batch *b) {
   (void)hipStreamSynchronize(b->stream);
   b->drop_graph();
   if (b->cap) (void)hipStreamDestroy(b->cap);
+  b->fields.release();
   void *ptrs[] = {b->buf[0], b->buf[1], b->gbuf,     b->urec,         b->uchk,  b->doms_d,
                   b->tiles_d, b->tile_begin_d, b->tile_end_d, b->partials, b->active_d,
                   b->n_active_d, b->state_d, b->scratch, b->multi_d};
@@ -650,6 +652,13 @@ int lbm_batch_moments(lbm_batch *b, int32_t dom, double *rho, double *u) {
   if (!valid(b)) return set_error(LBM_ESTATE, "invalid batch");
   if (dom < 0 || dom >= b->ndom) return set_error(LBM_EINVAL, "domain %d out of range", dom);
   const size_t fld = (size_t)b->dom[dom].N * sizeof(double);
+  if (double *h = b->fields.get(fld * (1 + b->D))) {
+    HIP_TRY(b->ops->moments(b->desc(dom), h, h + b->dom[dom].N, b->stream));
+    HIP_TRY(hipStreamSynchronize(b->stream));
+    if (rho) std::memcpy(rho, h, fld);
+    if (u) std::memcpy(u, h + b->dom[dom].N, fld * b->D);
+    return LBM_OK;
+  }
   int rc = b->need_scratch(fld * (1 + b->D));
   if (rc) return rc;
   double *rho_d = static_cast<double *>(b->scratch);

@@ -215,6 +215,33 @@ int sort_waves(int n, int Q, const int32_t *k, const double *phase, const double
                int ny, int nz, double *amp_out, double *phase_out, int *kyz, int *start,
                int *group_k);
 
+// Pinned host memory that a kernel writes a small read-back's fields into: the two copies to
+// pageable memory of a few kilobytes cost more than the fields.
+struct HostFields {
+  static constexpr size_t kMost = 1u << 20;
+  double *mem = nullptr;
+  size_t bytes = 0;
+  // memory for n bytes, or NULL (too many, or none to be had): copy from the device instead
+  double *get(size_t n) {
+    if (n > kMost) return nullptr;
+    if (n > bytes) {
+      release();
+      if (hipHostMalloc(reinterpret_cast<void **>(&mem), n, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        mem = nullptr;
+        return nullptr;
+      }
+      bytes = n;
+    }
+    return mem;
+  }
+  void release() {
+    if (mem) (void)hipHostFree(mem);
+    mem = nullptr;
+    bytes = 0;
+  }
+};
+
 // Error reporting shared by the runtime units (lbm_runtime.hip): records the message
 // for lbm_last_error() and returns status.
 int set_error(int status, const char *fmt, ...);

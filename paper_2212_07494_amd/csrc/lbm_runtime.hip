@@ -211,6 +211,7 @@ struct lbm_ctx {
         e = nullptr;
       }
   }
+  lbm::HostFields fields;  // small read-backs
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   size_t bytes = 0;
@@ -416,6 +417,7 @@ void release(lbm_ctx *c) {
   c->dfree(c->partials);
   c->dfree(c->mon_dev);
   c->dfree(c->scratch);
+  c->fields.release();
   if (c->mon_host) (void)hipHostFree(c->mon_host);
   if (c->mon_ev) (void)hipEventDestroy(c->mon_ev);
   c->drop_graphs();
@@ -473,7 +475,8 @@ int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const d
 
 // Monitor finalisation, the NaN fill and the stream-copy probe (lbm_aux.hip).
 namespace lbm {
-hipError_t finalize_monitors(const double *partials, int64_t nb, double *out, hipStream_t s);
+hipError_t finalize_monitors(const double *partials, int64_t nb, double *out, double *host,
+                             hipStream_t s);
 hipError_t fill_nan(void *p, size_t bytes, hipStream_t s);
 hipError_t graph_counter(int64_t *ctr, int64_t add, int set, hipStream_t s);
 hipError_t copy_probe(const void *src, void *dst, size_t bytes, int reps, int block,
@@ -482,10 +485,10 @@ hipError_t copy_probe(const void *src, void *dst, size_t bytes, int reps, int bl
 
 namespace {
 
-int refresh_monitors(lbm_ctx *c, int mode) {
+int refresh_monitors(lbm_ctx *c, int mode, double *host = nullptr) {
   lbm::LaunchDesc d = c->desc(c->last_scale);
   HIP_TRY(c->ops->monitor(d, c->uprev, mode, c->partials, c->stream));
-  HIP_TRY(lbm::finalize_monitors(c->partials, lbm::monitor_blocks(d), c->mon_dev, c->stream));
+  HIP_TRY(lbm::finalize_monitors(c->partials, lbm::monitor_blocks(d), c->mon_dev, host, c->stream));
   return LBM_OK;
 }
 
@@ -1100,21 +1103,25 @@ int lbm_monitors_get(lbm_ctx *c, lbm_monitors *mon) {
   if (!valid(c)) return fail(LBM_ESTATE, "invalid context");
   if (!mon) return fail(LBM_EINVAL, "mon is NULL");
   int mode;
+  double *host = nullptr;  // a fresh record is written there, the one at hand is copied
   if (c->dev_step == c->t) {
     // the in-step check of this time holds the record (refreshing it now would compare
     // the state with itself)
     mode = c->dev_mode;
   } else {
     mode = (c->uprev_time == c->t - 1) ? 4 : 2;
-    int rc = refresh_monitors(c, mode);
+    host = c->fields.get(lbm::MON_SLOTS * sizeof(double));
+    int rc = refresh_monitors(c, mode, host);
     if (rc) return rc;
     c->uprev_time = c->t;
     c->dev_step = c->t;
     c->dev_mode = mode;
   }
   double h[lbm::MON_SLOTS];
-  HIP_TRY(hipMemcpyAsync(h, c->mon_dev, sizeof(h), hipMemcpyDeviceToHost, c->stream));
+  if (!host)
+    HIP_TRY(hipMemcpyAsync(h, c->mon_dev, sizeof(h), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
+  if (host) std::memcpy(h, host, sizeof(h));
   c->check_pending = false;  // this record is the latest
   const lbm_monitors m = record_of(h, c->t, mode);
   c->mon = m;
@@ -1126,11 +1133,18 @@ int lbm_moments(lbm_ctx *c, double g_scale, double *rho, double *u) {
   if (!valid(c)) return fail(LBM_ESTATE, "invalid context");
   if (!std::isfinite(g_scale)) return fail(LBM_EINVAL, "g_scale is not finite");
   const size_t fld = (size_t)c->N * sizeof(double);
+  lbm::LaunchDesc d = c->desc(g_scale);
+  if (double *h = c->fields.get(fld * (1 + c->D))) {
+    HIP_TRY(c->ops->moments(d, h, h + c->N, c->stream));
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    if (rho) std::memcpy(rho, h, fld);
+    if (u) std::memcpy(u, h + c->N, fld * c->D);
+    return poll_checks(c, true);
+  }
   int rc = c->need_scratch(fld * (1 + c->D));
   if (rc) return rc;
   double *rho_d = static_cast<double *>(c->scratch);
   double *u_d = reinterpret_cast<double *>(static_cast<char *>(c->scratch) + fld);
-  lbm::LaunchDesc d = c->desc(g_scale);
   HIP_TRY(c->ops->moments(d, rho_d, u_d, c->stream));
   if (rho) HIP_TRY(hipMemcpyAsync(rho, rho_d, fld, hipMemcpyDeviceToHost, c->stream));
   if (u) HIP_TRY(hipMemcpyAsync(u, u_d, fld * c->D, hipMemcpyDeviceToHost, c->stream));
