@@ -105,12 +105,12 @@ inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
 
 // Fourier waves for waves_kernel (device arrays), sorted into groups of one k_x: group g's
 // waves are [group_start[g], group_start[g + 1]) and its wavenumber group_k[g]; per wave k_y
-// and k_z (kyz), the phase, and the Q amplitudes' (re, im) pairs.  Wavenumbers are reduced to
-// [0, n_a).
+// and k_z (kyz) and the Q amplitudes' (re, im) pairs, times e^{i phase}.  Wavenumbers are
+// reduced to [0, n_a).
 struct WaveTable {
   int ngroups;
   const int *group_start, *group_k, *kyz;
-  const double *phase, *amp;
+  const double *amp;
 };
 
 // One launch of the batched engine's persistent kernels.
@@ -212,8 +212,7 @@ inline const LatticeOps &ops_for(int lattice) {
 
 // lbm_runtime.hip: host side of a WaveTable (arrays of the sizes lbm_set_waves packs).
 int sort_waves(int n, int Q, const int32_t *k, const double *phase, const double *amp, int nx,
-               int ny, int nz, double *amp_out, double *phase_out, int *kyz, int *start,
-               int *group_k);
+               int ny, int nz, double *amp_out, int *kyz, int *start, int *group_k);
 
 // Pinned host memory that a kernel writes a small read-back's fields into: the two copies to
 // pageable memory of a few kilobytes cost more than the fields.

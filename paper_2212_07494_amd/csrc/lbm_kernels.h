@@ -463,9 +463,9 @@ __global__ void __launch_bounds__(256) scatter_kernel(S *__restrict__ f, Geom ge
 // Re[A_wi e^{i theta_w(x)}], theta_w(x) = 2 pi sum_a k_wa x_a / n_a + phase_w, stored as
 // f-bar_i - w_i shift, rounded once from binary64.
 //
-// The phase factors are products, e^{i theta} = e^{2 pi i k_x x / nx} e^{i psi}, psi = 2 pi
-// (k_y y / ny + k_z z / nz) + phase, and the waves come sorted by k_x (WaveTable), so the sum
-// over the waves of one k_x is taken once per row of nodes: B_gi = sum_{w in g} A_wi
+// The phase factors are products, e^{i theta} = e^{i phase} e^{2 pi i k_x x / nx} e^{i psi}, psi
+// = 2 pi (k_y y / ny + k_z z / nz); the host takes the first into the amplitude, and the waves
+// come sorted by k_x (WaveTable), so the sum over the waves of one k_x is taken once per row of nodes: B_gi = sum_{w in g} A_wi
 // e^{i psi_w}, and a node adds Re[B_gi e^{2 pi i k_g x / nx}] per group g.  The host folds
 // k_x and nx - k_x into one group (the real part of a wave is that of its conjugate), so an
 // expansion to fourth order with |k| <= 4 per mode has at most 17 groups for its 185 waves.
@@ -474,13 +474,15 @@ __global__ void __launch_bounds__(256) scatter_kernel(S *__restrict__ f, Geom ge
 // A workgroup takes WV_ROWS rows, one per wavefront, of WV_X nodes, two per lane.  For WV_G
 // groups at a time: their factors along x into LDS; the factors e^{i psi} of WV_SUB waves at a
 // time into LDS and from them the B_gi in registers (a thread holds one (g, i) for some of
-// the rows, so an amplitude is read once per WV_ROWS / PARTS rows); then the nodes' sums, B by
+// the rows, so an amplitude is read once per row group); then the nodes' sums, B by
 // broadcast.  With one sincos and 4 Q operations a wave and node (the sum as written) the
 // 128^3 D3Q27 start of 185 waves (9 groups) took 4.04 ms, bound by the binary64 ALU; grouped
-// 0.52 ms, of which writing the populations needs 0.07.  One workgroup of eight wavefronts fits a
-// compute unit (206 VGPRs), so its phases do not overlap; 256 threads and four rows, with
-// two workgroups, took the same time.
-constexpr int WV_ROWS = 8, WV_X = 128, WV_G = 8, WV_SUB = 64, WV_THREADS = 512;
+// 0.33 ms, of which writing the populations needs 0.07.  208 VGPRs leave two workgroups a
+// compute unit, whose phases overlap little, so latency is what remains: eight amplitudes and
+// eight B in flight together (0.52 -> 0.47 ms), most waves in one pass (WV_SUB 64: 0.45, 128:
+// 0.39).
+constexpr int WV_ROWS = 4, WV_X = 128, WV_SUB = 192, WV_THREADS = 256,
+              WV_LOADS = 8;
 
 // k x mod n for 0 <= k, x and k < n (x may run past n by less than WV_X): in 32 bits where
 // the product fits.
@@ -492,12 +494,12 @@ __device__ __forceinline__ int wave_mod(int k, int x, int n) {
 template <class L, class S>
 __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Geom geo,
                                                            WaveTable t, double base) {
-  constexpr int Q = L::Q, PAIRS = WV_G * Q;
+  constexpr int Q = L::Q, WV_G = Q > 32 ? 6 : 8, PAIRS = WV_G * Q;
   constexpr int PARTS = 4 * PAIRS <= WV_THREADS ? 4 : (2 * PAIRS <= WV_THREADS ? 2 : 1);
   constexpr int PR = WV_ROWS / PARTS;  // rows of a thread's B_gi
-  static_assert(PAIRS * PARTS <= WV_THREADS && WV_THREADS == 64 * WV_ROWS && WV_X == 128);
+  static_assert(PAIRS * PARTS <= WV_THREADS && WV_THREADS == 64 * WV_ROWS);
+  constexpr int NX = WV_X / 64;  // nodes of a lane
   __shared__ double2 ex[WV_G][WV_X], epsi[WV_SUB][WV_ROWS], B[WV_ROWS][WV_G][Q];
-  const double two_pi = 6.283185307179586;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int nchunk = (geo.nx + WV_X - 1) / WV_X;
@@ -505,15 +507,16 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
   const int row0 = (int)(blockIdx.x / nchunk) * WV_ROWS;
   const int x0 = (int)(blockIdx.x % nchunk) * WV_X;
   const int part = tid / PAIRS, pg = (tid - part * PAIRS) / Q, pi = (tid - part * PAIRS) % Q;
-  double acc[2][Q];
-  for (int i = 0; i < Q; ++i) acc[0][i] = acc[1][i] = 0.0;
+  double acc[NX][Q];
+  for (int j = 0; j < NX; ++j)
+    for (int i = 0; i < Q; ++i) acc[j][i] = 0.0;
   for (int g0 = 0; g0 < t.ngroups; g0 += WV_G) {
     const int gn = min(WV_G, t.ngroups - g0);
     for (int j = tid; j < gn * WV_X; j += WV_THREADS) {
       const int g = j / WV_X, x = x0 + j % WV_X;
       const int m = wave_mod(t.group_k[g0 + g], x, geo.nx);
       double s, c;
-      sincos(two_pi * (double(m) / geo.nx), &s, &c);
+      sincospi(2.0 * (double(m) / geo.nx), &s, &c);
       ex[g][j % WV_X] = make_double2(c, s);
     }
     double br[PR], bi[PR];
@@ -530,19 +533,23 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
           const int my = wave_mod(t.kyz[2 * w], y, geo.ny);
           const int mz = wave_mod(t.kyz[2 * w + 1], z, geo.nz);
           double s, c;
-          sincos(two_pi * (double(my) / geo.ny + double(mz) / geo.nz) + t.phase[w], &s, &c);
+          sincospi(2.0 * (double(my) / geo.ny + double(mz) / geo.nz), &s, &c);
           epsi[j / WV_ROWS][j % WV_ROWS] = make_double2(c, s);
         }
       }
       __syncthreads();
       const int we = min(w0 + WV_SUB, ghi);
-#pragma unroll 4
-      for (int w = max(w0, glo); w < we; ++w) {
-        const double2 a = reinterpret_cast<const double2 *>(t.amp)[(int64_t)w * Q + pi];
-        for (int r = 0; r < PR; ++r) {
-          const double2 e = epsi[w - w0][part * PR + r];
-          br[r] = fmadd(a.x, e.x, fmadd(-a.y, e.y, br[r]));
-          bi[r] = fmadd(a.x, e.y, fmadd(a.y, e.x, bi[r]));
+      for (int w = max(w0, glo); w < we; w += WV_LOADS) {
+        double2 am[WV_LOADS];  // loads in flight together
+        for (int v = 0; v < WV_LOADS; ++v)
+          am[v] = reinterpret_cast<const double2 *>(t.amp)[(int64_t)min(w + v, we - 1) * Q + pi];
+        for (int v = 0; v < WV_LOADS; ++v) {
+          if (w + v >= we) break;
+          for (int r = 0; r < PR; ++r) {
+            const double2 e = epsi[w + v - w0][part * PR + r];
+            br[r] = fmadd(am[v].x, e.x, fmadd(-am[v].y, e.y, br[r]));
+            bi[r] = fmadd(am[v].x, e.y, fmadd(am[v].y, e.x, bi[r]));
+          }
         }
       }
     }
@@ -550,12 +557,16 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
       for (int r = 0; r < PR; ++r) B[part * PR + r][pg][pi] = make_double2(br[r], bi[r]);
     __syncthreads();
     for (int g = 0; g < gn; ++g) {
-      const double2 e0 = ex[g][lane], e1 = ex[g][lane + 64];
-      static_for<Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        const double2 b = B[wave][g][i];
-        acc[0][i] = fmadd(b.x, e0.x, fmadd(-b.y, e0.y, acc[0][i]));
-        acc[1][i] = fmadd(b.x, e1.x, fmadd(-b.y, e1.y, acc[1][i]));
+      double2 e[NX];
+      for (int j = 0; j < NX; ++j) e[j] = ex[g][lane + 64 * j];
+      static_for<(Q + WV_LOADS - 1) / WV_LOADS>([&](auto C) {
+        constexpr int i0 = decltype(C)::value * WV_LOADS;
+        constexpr int n = Q - i0 < WV_LOADS ? Q - i0 : WV_LOADS;
+        double2 b[n];  // reads in flight together
+        for (int i = 0; i < n; ++i) b[i] = B[wave][g][i0 + i];
+        for (int i = 0; i < n; ++i)
+          for (int j = 0; j < NX; ++j)
+            acc[j][i0 + i] = fmadd(b[i].x, e[j].x, fmadd(-b[i].y, e[j].y, acc[j][i0 + i]));
       });
     }
     __syncthreads();
@@ -563,7 +574,7 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
   const int row = row0 + wave;
   if (row >= rows) return;
   const int y = row % geo.ny, z = row / geo.ny;
-  static_for<2>([&](auto J) {
+  static_for<NX>([&](auto J) {
     constexpr int j = decltype(J)::value;
     const int x = x0 + lane + 64 * j;
     if (x >= geo.nx) return;

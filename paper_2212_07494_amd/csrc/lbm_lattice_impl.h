@@ -156,10 +156,10 @@ struct Ops {
           for (int i = 0; i < L::Q && i < 31; ++i) {
             int c[3] = {x - L::E[i][0], y - L::E[i][1], z - L::E[i][2]};
             bool across_wall = false;
-            for (int a = 0; a < 3; ++a) {
-              if (c[a] >= 0 && c[a] < dims[a]) continue;
-              if (wall[a]) across_wall = true;
-              c[a] = (c[a] + dims[a]) % dims[a];
+            for (int a = 0; a < 3; ++a) {  // one wrap: links of one node
+              const bool lo = c[a] < 0, hi = c[a] >= dims[a];
+              across_wall |= (lo || hi) && wall[a];
+              c[a] += lo ? dims[a] : (hi ? -dims[a] : 0);
             }
             if (!across_wall && solid[((int64_t)c[2] * ny + c[1]) * nx + c[0]]) w |= 1u << i;
           }

@@ -433,11 +433,12 @@ void release(lbm_ctx *c) {
 }  // namespace
 
 // The waves of a WaveTable on the host: folded (a wave whose k_x exceeds nx - k_x becomes its
-// conjugate, k, phase and imaginary parts negated, with the same real part), sorted by k_x.
+// conjugate, k and imaginary part negated, with the same real part), sorted by k_x, the phase
+// taken into the amplitude.
 // Returns the number of groups, -1 if memory ran out.
 int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const double *amp,
-                    int nx, int ny, int nz, double *amp_out, double *phase_out, int *kyz,
-                    int *start, int *group_k) {
+                    int nx, int ny, int nz, double *amp_out, int *kyz, int *start,
+                    int *group_k) {
   const int dims[3] = {nx, ny, nz};
   auto reduced = [&](int w, int a, bool neg) {
     const int64_t m = ((int64_t)k[3 * w + a] % dims[a] + dims[a]) % dims[a];
@@ -462,11 +463,12 @@ int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const d
     }
     kyz[2 * j] = reduced(w, 1, neg);
     kyz[2 * j + 1] = reduced(w, 2, neg);
-    phase_out[j] = neg ? -phase[w] : phase[w];
+    const double cp = std::cos(phase[w]), sp = std::sin(phase[w]);
     for (int i = 0; i < Q; ++i) {
-      amp_out[2 * ((size_t)j * Q + i)] = amp[2 * ((size_t)w * Q + i)];
-      const double im = amp[2 * ((size_t)w * Q + i) + 1];
-      amp_out[2 * ((size_t)j * Q + i) + 1] = neg ? -im : im;
+      const double re = amp[2 * ((size_t)w * Q + i)], im = amp[2 * ((size_t)w * Q + i) + 1];
+      const double ri = re * sp + im * cp;
+      amp_out[2 * ((size_t)j * Q + i)] = re * cp - im * sp;
+      amp_out[2 * ((size_t)j * Q + i) + 1] = neg ? -ri : ri;
     }
   }
   start[g] = n;
@@ -1235,27 +1237,26 @@ int lbm_set_waves(lbm_ctx *c, int32_t nwaves, const int32_t *k, const double *ph
     if (!std::isfinite(amp[j])) return fail(LBM_EINVAL, "amp[%lld] is not finite", (long long)j);
   for (int w = 0; w < nwaves; ++w)
     if (!std::isfinite(phase[w])) return fail(LBM_EINVAL, "phase[%d] is not finite", w);
-  // sorted by k_x and folded (WaveTable), packed for one copy: amp, phase (binary64), then
-  // kyz, the groups' starts and their k_x (int32)
-  const size_t na = (size_t)2 * c->Q * nwaves, nd = na + nwaves, ni = (size_t)4 * nwaves + 1;
+  // sorted by k_x and folded (WaveTable), packed for one copy: amp (binary64), then kyz, the
+  // groups' starts and their k_x (int32)
+  const size_t nd = (size_t)2 * c->Q * nwaves, ni = (size_t)4 * nwaves + 1;
   std::vector<double> pack;
   try {
     pack.resize(nd + (ni + 1) / 2);
   } catch (const std::bad_alloc &) {
     return fail(LBM_ENOMEM, "host copy of %d waves", (int)nwaves);
   }
-  double *amp_h = pack.data(), *phase_h = amp_h + na;
+  double *amp_h = pack.data();
   int *kyz_h = reinterpret_cast<int *>(amp_h + nd);
   int *start_h = kyz_h + 2 * nwaves, *gk_h = start_h + nwaves + 1;
   const int ngroups = lbm::sort_waves(nwaves, c->Q, k, phase, amp, c->p.nx, c->p.ny, c->p.nz,
-                                      amp_h, phase_h, kyz_h, start_h, gk_h);
+                                      amp_h, kyz_h, start_h, gk_h);
   if (ngroups < 0) return fail(LBM_ENOMEM, "sorting %d waves", (int)nwaves);
   int rc = c->need_scratch(pack.size() * sizeof(double));
   if (rc) return rc;
   double *amp_d = static_cast<double *>(c->scratch);
   const int *kyz_d = reinterpret_cast<const int *>(amp_d + nd);
-  const lbm::WaveTable tab = {ngroups, kyz_d + 2 * nwaves, kyz_d + 3 * nwaves + 1,
-                              kyz_d,   amp_d + na,         amp_d};
+  const lbm::WaveTable tab = {ngroups, kyz_d + 2 * nwaves, kyz_d + 3 * nwaves + 1, kyz_d, amp_d};
   if (nwaves > 0)
     HIP_TRY(hipMemcpyAsync(amp_d, pack.data(), pack.size() * sizeof(double),
                            hipMemcpyHostToDevice, c->stream));
