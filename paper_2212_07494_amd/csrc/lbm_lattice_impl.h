@@ -147,24 +147,34 @@ struct Ops {
   }
   static void solid_words(const uint8_t *solid, int nx, int ny, int nz, const int wall[3],
                           uint32_t *out) {
+    // links of one node (Q <= 27): one wrap; away from the faces a source is a constant
+    // distance behind
     const int dims[3] = {nx, ny, nz};
     for (int z = 0; z < nz; ++z)
-      for (int y = 0; y < ny; ++y)
+      for (int y = 0; y < ny; ++y) {
+        const bool edge = y == 0 || y == ny - 1 || (L::D == 3 && (z == 0 || z == nz - 1));
         for (int x = 0; x < nx; ++x) {
           const int64_t n = ((int64_t)z * ny + y) * nx + x;
           uint32_t w = solid[n] ? SOLID_NODE : 0u;
-          for (int i = 0; i < L::Q && i < 31; ++i) {
-            int c[3] = {x - L::E[i][0], y - L::E[i][1], z - L::E[i][2]};
-            bool across_wall = false;
-            for (int a = 0; a < 3; ++a) {  // one wrap: links of one node
-              const bool lo = c[a] < 0, hi = c[a] >= dims[a];
-              across_wall |= (lo || hi) && wall[a];
-              c[a] += lo ? dims[a] : (hi ? -dims[a] : 0);
+          if (!edge && x > 0 && x < nx - 1) {
+            for (int i = 0; i < L::Q && i < 31; ++i)
+              w |= (uint32_t)(solid[n - ((int64_t)L::E[i][2] * ny + L::E[i][1]) * nx - L::E[i][0]] != 0)
+                   << i;
+          } else {
+            for (int i = 0; i < L::Q && i < 31; ++i) {
+              int c[3] = {x - L::E[i][0], y - L::E[i][1], z - L::E[i][2]};
+              bool across_wall = false;
+              for (int a = 0; a < 3; ++a) {
+                const bool lo = c[a] < 0, hi = c[a] >= dims[a];
+                across_wall |= (lo || hi) && wall[a];
+                c[a] += lo ? dims[a] : (hi ? -dims[a] : 0);
+              }
+              if (!across_wall && solid[((int64_t)c[2] * ny + c[1]) * nx + c[0]]) w |= 1u << i;
             }
-            if (!across_wall && solid[((int64_t)c[2] * ny + c[1]) * nx + c[0]]) w |= 1u << i;
           }
           out[n] = w;
         }
+      }
   }
   static hipError_t gather(const LaunchDesc &d, const int64_t *nodes, int64_t nn, double *out,
                            hipStream_t s) {
