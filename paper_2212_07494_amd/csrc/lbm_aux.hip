@@ -80,20 +80,29 @@ __global__ void fill_ff_kernel(uint4 *__restrict__ p, int64_t n16, unsigned char
 // Below this window coherence a stalled residual counts as the round-off floor.
 constexpr double kFloorCoherence = 0.03;
 
-// Per-domain convergence decision after a compare pass (one thread per domain).
+// Per-domain convergence decision after a compare pass: one wavefront per domain, whose
+// lanes take its tiles in turn and combine in a fixed tree (one thread a domain waited for
+// each tile's partials: 46 us for 512 domains).
 __global__ void decide_kernel(const int *__restrict__ tile_begin, const int *__restrict__ tile_end,
                               const double *__restrict__ partials, DomState *__restrict__ st,
                               int *__restrict__ active, int *__restrict__ n_active, int ndom,
                               double tol, int stall_checks, int steps) {
-  const int d = blockIdx.x * blockDim.x + threadIdx.x;
+  const int d = (blockIdx.x * blockDim.x + threadIdx.x) >> 6, lane = threadIdx.x & 63;
   if (d >= ndom || !active[d]) return;
   double du2 = 0.0, u2 = 0.0, bad = 0.0, duk2 = 0.0;
-  for (int t = tile_begin[d]; t < tile_end[d]; ++t) {
+  for (int t = tile_begin[d] + lane; t < tile_end[d]; t += 64) {
     du2 += partials[(int64_t)t * BATCH_PARTIALS + BP_DU2];
     u2 += partials[(int64_t)t * BATCH_PARTIALS + BP_U2];
     bad += partials[(int64_t)t * BATCH_PARTIALS + BP_BAD];
     duk2 += partials[(int64_t)t * BATCH_PARTIALS + BP_DUK2];
   }
+  for (int o = 32; o > 0; o >>= 1) {
+    du2 += __shfl_xor(du2, o, 64);
+    u2 += __shfl_xor(u2, o, 64);
+    bad += __shfl_xor(bad, o, 64);
+    duk2 += __shfl_xor(duk2, o, 64);
+  }
+  if (lane != 0) return;
   DomState s = st[d];
   s.steps += steps;
   const double r = u2 > 0.0 ? sqrt(du2 / u2) : (du2 > 0.0 ? INFINITY : 0.0);
@@ -146,7 +155,7 @@ __global__ void add_steps_kernel(const int *__restrict__ active, DomState *__res
 hipError_t decide_domains(const int *tile_begin, const int *tile_end, const double *partials,
                           void *state, int *active, int *n_active, int ndom, double tol,
                           int stall_checks, int steps, hipStream_t s) {
-  hipLaunchKernelGGL(decide_kernel, dim3((ndom + 255) / 256), dim3(256), 0, s, tile_begin,
+  hipLaunchKernelGGL(decide_kernel, dim3((ndom + 3) / 4), dim3(256), 0, s, tile_begin,
                      tile_end, partials, static_cast<DomState *>(state), active, n_active, ndom,
                      tol, stall_checks, steps);
   return hipGetLastError();

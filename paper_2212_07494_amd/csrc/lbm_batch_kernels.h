@@ -160,10 +160,17 @@ __global__ void __launch_bounds__(256)
       const int node = (z * dm.ny + y) * dm.nx + x;
       T d[L::Q];
       const S *fd = f + dm.base;
-      static_for<L::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        d[i] = T(fd[pull_slot<L, i>(x, y, z, geo, 0u)]);
-      });
+      if (tile_fast<S>(tile, dm, geo)) {
+        static_for<L::Q>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          d[i] = T(*pull_ptr_periodic<L, i>(fd, x, y, z, geo));
+        });
+      } else {
+        static_for<L::Q>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          d[i] = T(fd[pull_slot<L, i>(x, y, z, geo, 0u)]);
+        });
+      }
       T g[3];
       batch_force<T>(gbuf, dm, x, y, z, node, L::D, g);
       const Macro<T> M = macroscopic<L>(d, shift, g);

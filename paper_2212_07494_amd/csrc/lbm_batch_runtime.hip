@@ -42,6 +42,16 @@ void block_shape(int nx, int &bx, int &by) {
 // Tile policy 1: linear tiles of 256 consecutive nodes (any domain width).
 constexpr int kLinearTiles = 1;
 
+// Launch of the single steps before any tuning: one workgroup a linear tile, which leaves no
+// lanes idle and lets the hardware balance the tiles (a persistent grid of eight workgroups a
+// compute unit walking row tiles against it, us a step: 512 D2Q9 domains FP32-shifted 118 and
+// 76, FP64 215 and 148; 32 D3Q19 boxes 316 and 158, 16 D3Q27 boxes FP64 335 and 226); plain
+// stores while the two buffers fit the last-level cache (64 D2Q9 domains 13.5 against 15.8),
+// else non-temporal ones (32 D3Q19 boxes 158 against 166).
+lbm_batch_tuning default_tuning(size_t pop_bytes) {
+  return {kLinearTiles, 0, 2 * pop_bytes <= (size_t(320) << 20) ? 0 : 1};
+}
+
 int tile_width(int policy, int nx) {
   if (policy) return policy;
   return nx > 128 ? 256 : (nx > 64 ? 128 : 64);
@@ -81,7 +91,7 @@ struct lbm_batch {
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   size_t bytes = 0;
-  lbm_batch_tuning tune{0, 8, 1};
+  lbm_batch_tuning tune{0, 8, 1};  // set by size at init (default_tuning)
   int ncu = 256, lds_cu = 0;
   // several steps a launch (D2Q9): steps (0: none), tiles and their LDS
   int multi_K = 0, nmulti = 0;
@@ -526,6 +536,7 @@ int lbm_batch_init(const lbm_domain *domains, int32_t ndom, int32_t lattice, int
   if (hipMemcpyAsync(b->gbuf, gconv.data(), gconv.size(), hipMemcpyHostToDevice, b->stream) !=
       hipSuccess)
     return bail(set_error(LBM_EDEVICE, "uploading force tables failed"));
+  b->tune = default_tuning(pop);
   if ((rc = build_tiles(b))) return bail(rc);
   if ((rc = build_multi(b))) return bail(rc);
   if ((rc = reset_states(b))) return bail(rc);
