@@ -344,14 +344,18 @@ int build_multi(lbm_batch *b) {
   if (!rows) return LBM_OK;
   std::vector<lbm::BatchMultiTile> tiles;
   int tallest = 0;
-  for (int d = 0; d < b->ndom; ++d) {
-    const lbm::BatchDom &m = b->dom[d];
-    const int ntx = lbm::multi_columns(m.nx, K), nty = (m.ny + rows - 1) / rows;
-    const int ox = (m.nx + ntx - 1) / ntx, oy = (m.ny + nty - 1) / nty;
-    tallest = std::max(tallest, oy);
-    for (int y0 = 0; y0 < m.ny; y0 += oy)
-      for (int x0 = 0; x0 < m.nx; x0 += ox)
-        tiles.push_back({d, x0, y0, std::min(ox, m.nx - x0), std::min(oy, m.ny - y0)});
+  try {
+    for (int d = 0; d < b->ndom; ++d) {
+      const lbm::BatchDom &m = b->dom[d];
+      const int ntx = lbm::multi_columns(m.nx, K), nty = (m.ny + rows - 1) / rows;
+      const int ox = (m.nx + ntx - 1) / ntx, oy = (m.ny + nty - 1) / nty;
+      tallest = std::max(tallest, oy);
+      for (int y0 = 0; y0 < m.ny; y0 += oy)
+        for (int x0 = 0; x0 < m.nx; x0 += ox)
+          tiles.push_back({d, x0, y0, std::min(ox, m.nx - x0), std::min(oy, m.ny - y0)});
+    }
+  } catch (const std::bad_alloc &) {
+    return set_error(LBM_ENOMEM, "host memory for the tiles");
   }
   int rc = b->dalloc(&b->multi_d, tiles.size() * sizeof(tiles[0]));
   if (rc) return rc;
