@@ -1,4 +1,5 @@
-// Launchers of the D2Q9 multi-step kernels (lbm_multistep.h).
+// Launchers of the D2Q9 multi-step kernels (lbm_multistep.h); included by lbm_d2q9.hip only.
+#pragma once
 #include "lbm_multistep.h"
 
 namespace lbm {

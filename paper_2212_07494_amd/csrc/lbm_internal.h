@@ -189,7 +189,7 @@ hipError_t decide_domains(const int *tile_begin, const int *tile_end, const doub
                           int stall_checks, int steps, hipStream_t s);
 hipError_t add_domain_steps(const int *active, void *state, int ndom, int64_t n, hipStream_t s);
 
-// lbm_d2q9_multi.hip
+// lbm_d2q9_multi.h (part of lbm_d2q9.hip)
 MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu);
 hipError_t multi_step_d2q9(const LaunchDesc &, const MultiPlan &, int k, const double *gs,
                            hipStream_t);
