@@ -115,12 +115,22 @@ int default_variant(size_t pop_bytes) { return 2 * pop_bytes <= kCachedBytes ? 9
 // Block shape: up to 256 threads of whole wavefronts along x, the widest rows among those
 // that leave the fewest lanes idle (192 columns: 64 x 4 rather than 128 x 2, D3Q27 FP64 516
 // against 631 us a step, FP32-shifted 263 against 317, D3Q19 FP32-shifted 185 against 225).
+// A ragged width keeps two rows or more (linear_blocks).
 void block_shape(int nx, int &bx, int &by) {
   bx = 64;
   for (int w : {128, 256})
-    if ((int64_t)(nx + w - 1) / w * w <= (int64_t)(nx + bx - 1) / bx * bx) bx = w;
+    if ((nx % 64 == 0 || w < 256) &&
+        (int64_t)(nx + w - 1) / w * w <= (int64_t)(nx + bx - 1) / bx * bx)
+      bx = w;
   by = 256 / bx;
 }
+
+// Whether a step's blocks take consecutive nodes: on ragged widths, where rows would leave
+// lanes idle, unless the block is a single row.  So the tuner measures both kinds: D3Q27 of
+// 72 columns FP32-shifted 27.3 us linear against 34.2 in rows (FP16-shifted 23.3 / 32.4), but
+// tuned 120 columns FP16-shifted 31.1 / 28.1, 111 columns FP64 rMRT 96.6 / 92.9 (another card
+// 89.3 / 92.7).
+bool linear_blocks(int nx, int by) { return nx % 64 != 0 && by > 1; }
 
 }  // namespace
 
@@ -305,7 +315,7 @@ struct lbm_ctx {
     // for them; consecutive nodes of the layer fill them all (D3Q19 BGK FP64 131 x 67 x 59
     // with walls: 39.7 -> 31.5 us a step as launched by default then, 160^3 FP64 267 -> 215;
     // 100^3 FP32-shifted 35.4 -> 29.9)
-    d.linear = p.nx % 64 != 0;
+    d.linear = linear_blocks(p.nx, by);
     d.lds_pad = lds_for_cap(kWaveCaps[variant / kBaseVariants], bx, by, lds_cu, lds_block);
     return d;
   }
