@@ -289,7 +289,8 @@ int lbm_save(lbm_ctx *c, const char *path);
 int lbm_load(lbm_ctx *c, const char *path);
 
 /* Launch configuration of the step kernel: block shape bx x by (bx in {64, 128, 256},
- * bx * by <= 256) and variant 0..59, whose base b = variant % 12 selects the memory
+ * bx * by <= 256; 64 x 2, where nx is no multiple of 64, takes 128 consecutive nodes of a
+ * layer instead of two rows) and variant 0..59, whose base b = variant % 12 selects the memory
  * access b % 3 (0 plain loads and stores, 1 non-temporal stores, 2 non-temporal loads and
  * stores); (b / 3) odd also lets workgroups that cannot bounce back (no solid nodes, away
  * from wall faces) address each population plane through a scalar base and 32-bit
@@ -309,7 +310,8 @@ int lbm_set_tuning(lbm_ctx *c, const lbm_tuning *t);
 int lbm_get_tuning(const lbm_ctx *c, lbm_tuning *t);
 
 /* Time every block shape with the variants 0..11 for `steps` steps (>= 1), then the
- * fastest of those with each wave cap (variant + 12 k, k = 1..4), and keep the fastest
+ * fastest of those (of the rows and of the consecutive nodes) with each wave cap
+ * (variant + 12 k, k = 1..4), and keep the fastest
  * of all.  The state is saved before and restored after, so the simulation is
  * unchanged.  best and
  * best_ms (time per step of the winner) may be NULL.  Synchronises the stream and

@@ -112,25 +112,20 @@ using lbm::ops_for;
 constexpr size_t kCachedBytes = 320u << 20;
 int default_variant(size_t pop_bytes) { return 2 * pop_bytes <= kCachedBytes ? 9 : 4; }
 
-// Block shape: up to 256 threads of whole wavefronts along x, the widest rows among those
-// that leave the fewest lanes idle (192 columns: 64 x 4 rather than 128 x 2, D3Q27 FP64 516
-// against 631 us a step, FP32-shifted 263 against 317, D3Q19 FP32-shifted 185 against 225).
-// A ragged width keeps two rows or more (linear_blocks).
+// Block shape: 256 threads of whole wavefronts along x, the widest rows among those that
+// leave the fewest lanes idle (192 columns: 64 x 4 rather than 128 x 2, D3Q27 FP64 516 against
+// 631 us a step, FP32-shifted 263 against 317, D3Q19 FP32-shifted 185 against 225); on ragged
+// widths 64 x 2, whose steps take consecutive nodes (linear_blocks).
 void block_shape(int nx, int &bx, int &by) {
-  bx = 64;
-  for (int w : {128, 256})
-    if ((nx % 64 == 0 || w < 256) &&
-        (int64_t)(nx + w - 1) / w * w <= (int64_t)(nx + bx - 1) / bx * bx)
-      bx = w;
-  by = 256 / bx;
+  bx = nx % 128 ? 64 : nx % 256 ? 128 : 256;
+  by = nx % 64 ? 2 : 256 / bx;
 }
 
-// Whether a step's blocks take consecutive nodes: on ragged widths, where rows would leave
-// lanes idle, unless the block is a single row.  So the tuner measures both kinds: D3Q27 of
-// 72 columns FP32-shifted 27.3 us linear against 34.2 in rows (FP16-shifted 23.3 / 32.4), but
-// tuned 120 columns FP16-shifted 31.1 / 28.1, 111 columns FP64 rMRT 96.6 / 92.9 (another card
-// 89.3 / 92.7).
-bool linear_blocks(int nx, int by) { return nx % 64 != 0 && by > 1; }
+// Whether a step's blocks take consecutive nodes: on ragged widths, where rows leave lanes
+// idle, blocks of 64 x 2; the other shapes stay rows.  The tuner measures both: D3Q27 of 72
+// columns FP32-shifted 27 us linear against 34 in rows, 150 columns FP64 111 / 128 tuned, but
+// tuned 120 columns FP16-shifted 31.1 / 28.3, 160 columns FP32-shifted 61.7 / 58.6.
+bool linear_blocks(int nx, int bx, int by) { return nx % 64 != 0 && bx == 64 && by == 2; }
 
 }  // namespace
 
@@ -321,9 +316,8 @@ struct lbm_ctx {
     d.xcd = base / (2 * kMemVariants);
     // rows that fill no wavefront leave its last lanes idle, and as many memory requests
     // for them; consecutive nodes of the layer fill them all (D3Q19 BGK FP64 131 x 67 x 59
-    // with walls: 39.7 -> 31.5 us a step as launched by default then, 160^3 FP64 267 -> 215;
-    // 100^3 FP32-shifted 35.4 -> 29.9)
-    d.linear = linear_blocks(p.nx, by);
+    // with walls: 39.7 -> 31.5 us a step as launched by default then, 160^3 FP64 267 -> 215)
+    d.linear = linear_blocks(p.nx, bx, by);
     d.lds_pad = lds_for_cap(kWaveCaps[variant / kBaseVariants], bx, by, lds_cu, lds_block);
     return d;
   }
@@ -1550,8 +1544,8 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
   HIP_TRY(hipMemcpyAsync(c->scratch, c->buf[c->cur], pop_bytes, hipMemcpyDeviceToDevice,
                          c->stream));
   const lbm_tuning start = {c->bx, c->by, c->variant};
-  lbm_tuning win = start;
-  float win_ms = -1.0f;
+  lbm_tuning kind[2] = {start, start};  // best of the blocks of rows, of the linear ones
+  float kind_ms[2] = {-1.0f, -1.0f};
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
@@ -1581,9 +1575,10 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
       return false;
     }
     ms /= steps;
-    if (win_ms < 0 || ms < win_ms) {
-      win_ms = ms;
-      win = {bx, by, v};
+    const int linear = linear_blocks(c->p.nx, bx, by);
+    if (kind_ms[linear] < 0 || ms < kind_ms[linear]) {
+      kind_ms[linear] = ms;
+      kind[linear] = {bx, by, v};
     }
     return true;
   };
@@ -1597,11 +1592,14 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
     }
     if (status) break;
   }
-  // ... then the winner held to fewer waves per SIMD
-  const lbm_tuning stage1 = win;
-  for (int k = 1; k < kNumCaps && !status; ++k)
-    if (lds_for_cap(kWaveCaps[k], stage1.bx, stage1.by, c->lds_cu, c->lds_block))
-      trial(stage1.bx, stage1.by, stage1.variant % kBaseVariants + k * kBaseVariants);
+  // ... then the winner held to fewer waves per SIMD (on ragged widths the best rows and the
+  // best linear blocks, which gain differently: D3Q27 FP32-shifted of 150 columns 68.4 us
+  // with the caps of the faster of the two alone, 62.7 with both)
+  const lbm_tuning stage1[2] = {kind[0], kind[1]};
+  for (int i = 0; i < 2; ++i)
+    for (int k = 1; k < kNumCaps && kind_ms[i] >= 0 && !status; ++k)
+      if (lds_for_cap(kWaveCaps[k], stage1[i].bx, stage1[i].by, c->lds_cu, c->lds_block))
+        trial(stage1[i].bx, stage1[i].by, stage1[i].variant % kBaseVariants + k * kBaseVariants);
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   // restore the state into the buffer it came from
@@ -1613,6 +1611,9 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
     lbm_set_tuning(c, &start);
     return status;
   }
+  const int lin = kind_ms[0] < 0 || (kind_ms[1] >= 0 && kind_ms[1] < kind_ms[0]);
+  const lbm_tuning win = kind[lin];
+  const float win_ms = kind_ms[lin];
   rc = lbm_set_tuning(c, &win);
   if (rc) return rc;
   if (best) *best = win;

@@ -53,7 +53,9 @@ def test_linear_blocks(lat, shape, walls, solid):
                         store16=bool(o._p.store16), solid=mask)
         fo = o.run(f0.astype(o.dtype), g, 2).astype(np.float64)
         with L.Lattice(lat, "smrt", storage, shape, walls, TAU, g_field=g, solid=mask) as gpu:
-            for bx, by, v in [(64, 1, 0), (64, 4, 4), (128, 2, 8), (256, 1, 9), (128, 1, 10)]:
+            # 64 x 2 takes consecutive nodes on these widths, the others rows
+            for bx, by, v in [(64, 2, 0), (64, 2, 4), (64, 2, 9), (64, 2, 14), (64, 1, 0),
+                              (64, 4, 4), (128, 2, 8), (256, 1, 9), (128, 1, 10)]:
                 gpu.tune(bx, by, v)
                 gpu.set_populations(f0)
                 gpu.step(2)
