@@ -7,6 +7,8 @@
 
 #include <cstdint>
 
+#include "lbm_plan.h"
+
 namespace lbm {
 
 // Slots of a monitor record (binary64), per block partial and after finalisation: mass,
@@ -102,16 +104,6 @@ inline int multi_steps(int ny, bool wy) { return wy || ny >= 12 ? MULTI_STEPS : 
 inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
   return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
 }
-
-// Fourier waves for waves_kernel (device arrays), sorted into groups of one k_x: group g's
-// waves are [group_start[g], group_start[g + 1]) and its wavenumber group_k[g]; per wave k_y
-// and k_z (kyz) and the Q amplitudes' (re, im) pairs, times e^{i phase}.  Wavenumbers are
-// reduced to [0, n_a).
-struct WaveTable {
-  int ngroups;
-  const int *group_start, *group_k, *kyz;
-  const double *amp;
-};
 
 // One launch of the batched engine's persistent kernels.
 struct BatchLaunch {
@@ -212,7 +204,8 @@ inline const LatticeOps &ops_for(int lattice) {
 
 // lbm_runtime.hip: host side of a WaveTable (arrays of the sizes lbm_set_waves packs).
 int sort_waves(int n, int Q, const int32_t *k, const double *phase, const double *amp, int nx,
-               int ny, int nz, double *amp_out, int *kyz, int *start, int *group_k);
+               int ny, int nz, double *amp_out, int *k_out, int *start, int *group_k,
+               int *longest);
 
 // Pinned host memory that a kernel writes a small read-back's fields into: the two copies to
 // pageable memory of a few kilobytes cost more than the fields.

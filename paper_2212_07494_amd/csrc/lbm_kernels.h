@@ -481,8 +481,7 @@ __global__ void __launch_bounds__(256) scatter_kernel(S *__restrict__ f, Geom ge
 // compute unit, whose phases overlap little, so latency is what remains: eight amplitudes and
 // eight B in flight together (0.52 -> 0.47 ms), most waves in one pass (WV_SUB 64: 0.45, 128:
 // 0.39).
-constexpr int WV_ROWS = 4, WV_X = 128, WV_SUB = 192, WV_THREADS = 256,
-              WV_LOADS = 8;
+constexpr int WV_SUB = 192, WV_LOADS = 8;
 
 // k x mod n for 0 <= k, x and k < n (x may run past n by less than WV_X): in 32 bits where
 // the product fits.
@@ -530,8 +529,9 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
         const int w = w0 + j / WV_ROWS, row = min(row0 + j % WV_ROWS, rows - 1);
         if (w < whi) {
           const int y = row % geo.ny, z = row / geo.ny;
-          const int my = wave_mod(t.kyz[2 * w], y, geo.ny);
-          const int mz = wave_mod(t.kyz[2 * w + 1], z, geo.nz);
+          const int4 k = reinterpret_cast<const int4 *>(t.k)[w];
+          const int my = wave_mod(k.y, y, geo.ny);
+          const int mz = wave_mod(k.z, z, geo.nz);
           double s, c;
           sincospi(2.0 * (double(my) / geo.ny + double(mz) / geo.nz), &s, &c);
           epsi[j / WV_ROWS][j % WV_ROWS] = make_double2(c, s);
@@ -584,6 +584,41 @@ __global__ void __launch_bounds__(WV_THREADS) waves_kernel(S *__restrict__ f, Ge
       constexpr int i = decltype(I)::value;
       f[pull_slot<L, i>(x, y, z, geo, sm)] = S(Tab<L, double>::w(i) * base + acc[j][i]);
     });
+  });
+}
+
+// The same state, a node per thread and a sincos per wave and node: rows of few nodes, or few
+// waves, do not repay the rows' sums above (waves_by_node).
+template <class L, class S>
+__global__ void __launch_bounds__(WV_THREADS) waves_node_kernel(S *__restrict__ f, Geom geo,
+                                                                WaveTable t, double base) {
+  constexpr int Q = L::Q;
+  const int64_t node = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (node >= geo.N) return;
+  const int n = (int)node, row = n / geo.nx;
+  const int x = n - row * geo.nx, y = row % geo.ny, z = row / geo.ny;
+  const uint32_t sm = node_mask(geo, n);
+  if (sm & SOLID_NODE) return;
+  double acc[Q];
+  for (int i = 0; i < Q; ++i) acc[i] = 0.0;
+  // k x / n in [-1/2, 1/2)
+  auto turn = [](int k, int x, int n) -> double {
+    const int m = wave_mod(k, x, n);
+    return double(m < n - m ? m : m - n) / n;
+  };
+  for (int w = 0; w < t.nwaves; ++w) {
+    const int4 k = reinterpret_cast<const int4 *>(t.k)[w];
+    double s, c;
+    sincospi(2.0 * (turn(k.x, x, geo.nx) + (turn(k.y, y, geo.ny) + turn(k.z, z, geo.nz))), &s, &c);
+    const double *a = t.amp + (int64_t)2 * Q * w;
+    static_for<Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      acc[i] = fmadd(a[2 * i], c, fmadd(-a[2 * i + 1], s, acc[i]));
+    });
+  }
+  static_for<Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    f[pull_slot<L, i>(x, y, z, geo, sm)] = S(Tab<L, double>::w(i) * base + acc[i]);
   });
 }
 

@@ -200,8 +200,14 @@ struct Ops {
     return with_types(d.storage, [&](auto *sp, auto *) -> hipError_t {
       using S = std::remove_pointer_t<decltype(sp)>;
       const int64_t rows = (int64_t)d.geo.ny * d.geo.nz;
-      const int64_t blocks = (rows + WV_ROWS - 1) / WV_ROWS * ((d.geo.nx + WV_X - 1) / WV_X);
-      hipLaunchKernelGGL((waves_kernel<L, S>), dim3((unsigned)blocks), dim3(WV_THREADS), 0, s,
+      if (waves_by_node(t, L::Q, d.geo.nx)) {
+        const unsigned blocks = (unsigned)(((int64_t)d.geo.N + WV_THREADS - 1) / WV_THREADS);
+        hipLaunchKernelGGL((waves_node_kernel<L, S>), dim3(blocks), dim3(WV_THREADS), 0, s,
+                           static_cast<S *>(d.fout), geom_of(d), t, base);
+        return hipGetLastError();
+      }
+      const unsigned blocks = (unsigned)waves_blocks(d.geo.nx, rows);
+      hipLaunchKernelGGL((waves_kernel<L, S>), dim3(blocks), dim3(WV_THREADS), 0, s,
                          static_cast<S *>(d.fout), geom_of(d), t, base);
       return hipGetLastError();
     });

@@ -453,8 +453,8 @@ void release(lbm_ctx *c) {
 // taken into the amplitude.
 // Returns the number of groups, -1 if memory ran out.
 int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const double *amp,
-                    int nx, int ny, int nz, double *amp_out, int *kyz, int *start,
-                    int *group_k) {
+                    int nx, int ny, int nz, double *amp_out, int *k_out, int *start,
+                    int *group_k, int *longest) {
   const int dims[3] = {nx, ny, nz};
   auto reduced = [&](int w, int a, bool neg) {
     const int64_t m = ((int64_t)k[3 * w + a] % dims[a] + dims[a]) % dims[a];
@@ -477,8 +477,11 @@ int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const d
       start[g] = j;
       group_k[g++] = order[j].first;
     }
-    kyz[2 * j] = reduced(w, 1, neg);
-    kyz[2 * j + 1] = reduced(w, 2, neg);
+    int *kj = k_out + 4 * (size_t)j;
+    kj[0] = order[j].first;
+    kj[1] = reduced(w, 1, neg);
+    kj[2] = reduced(w, 2, neg);
+    kj[3] = 0;
     const double cp = std::cos(phase[w]), sp = std::sin(phase[w]);
     for (int i = 0; i < Q; ++i) {
       const double re = amp[2 * ((size_t)w * Q + i)], im = amp[2 * ((size_t)w * Q + i) + 1];
@@ -488,6 +491,8 @@ int lbm::sort_waves(int n, int Q, const int32_t *k, const double *phase, const d
     }
   }
   start[g] = n;
+  *longest = 0;
+  for (int j = 0; j < g; ++j) *longest = std::max(*longest, start[j + 1] - start[j]);
   return g;
 }
 
@@ -1253,9 +1258,9 @@ int lbm_set_waves(lbm_ctx *c, int32_t nwaves, const int32_t *k, const double *ph
     if (!std::isfinite(amp[j])) return fail(LBM_EINVAL, "amp[%lld] is not finite", (long long)j);
   for (int w = 0; w < nwaves; ++w)
     if (!std::isfinite(phase[w])) return fail(LBM_EINVAL, "phase[%d] is not finite", w);
-  // sorted by k_x and folded (WaveTable), packed for one copy: amp (binary64), then kyz, the
+  // sorted by k_x and folded (WaveTable), packed for one copy: amp (binary64), then k, the
   // groups' starts and their k_x (int32)
-  const size_t nd = (size_t)2 * c->Q * nwaves, ni = (size_t)4 * nwaves + 1;
+  const size_t nd = (size_t)2 * c->Q * nwaves, ni = (size_t)6 * nwaves + 1;
   std::vector<double> pack;
   try {
     pack.resize(nd + (ni + 1) / 2);
@@ -1263,16 +1268,17 @@ int lbm_set_waves(lbm_ctx *c, int32_t nwaves, const int32_t *k, const double *ph
     return fail(LBM_ENOMEM, "host copy of %d waves", (int)nwaves);
   }
   double *amp_h = pack.data();
-  int *kyz_h = reinterpret_cast<int *>(amp_h + nd);
-  int *start_h = kyz_h + 2 * nwaves, *gk_h = start_h + nwaves + 1;
+  int *k_h = reinterpret_cast<int *>(amp_h + nd), *start_h = k_h + 4 * (size_t)nwaves;
+  int longest = 0;
   const int ngroups = lbm::sort_waves(nwaves, c->Q, k, phase, amp, c->p.nx, c->p.ny, c->p.nz,
-                                      amp_h, kyz_h, start_h, gk_h);
+                                      amp_h, k_h, start_h, start_h + nwaves + 1, &longest);
   if (ngroups < 0) return fail(LBM_ENOMEM, "sorting %d waves", (int)nwaves);
   int rc = c->need_scratch(pack.size() * sizeof(double));
   if (rc) return rc;
   double *amp_d = static_cast<double *>(c->scratch);
-  const int *kyz_d = reinterpret_cast<const int *>(amp_d + nd);
-  const lbm::WaveTable tab = {ngroups, kyz_d + 2 * nwaves, kyz_d + 3 * nwaves + 1, kyz_d, amp_d};
+  const int *k_d = reinterpret_cast<const int *>(amp_d + nd);
+  const int *start_d = k_d + 4 * (size_t)nwaves;
+  const lbm::WaveTable tab = {nwaves, ngroups, longest, start_d, start_d + nwaves + 1, k_d, amp_d};
   if (nwaves > 0)
     HIP_TRY(hipMemcpyAsync(amp_d, pack.data(), pack.size() * sizeof(double),
                            hipMemcpyHostToDevice, c->stream));

@@ -1,0 +1,22 @@
+// Prints what the launch rules (lbm_plan.h) decide: one query a line on standard input, one
+// answer a line.
+#include <cstdio>
+#include <cstring>
+
+#include "lbm_plan.h"
+
+int main() {
+  char what[32];
+  while (std::scanf("%31s", what) == 1) {
+    if (!std::strcmp(what, "waves_by_node")) {  // nwaves ngroups longest Q nx
+      lbm::WaveTable t{};
+      int Q, nx;
+      if (std::scanf("%d %d %d %d %d", &t.nwaves, &t.ngroups, &t.longest, &Q, &nx) != 5)
+        return 1;
+      std::printf("%d\n", (int)lbm::waves_by_node(t, Q, nx));
+    } else {
+      return 1;
+    }
+  }
+  return 0;
+}
