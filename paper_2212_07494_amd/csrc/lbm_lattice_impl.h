@@ -200,7 +200,7 @@ struct Ops {
     return with_types(d.storage, [&](auto *sp, auto *) -> hipError_t {
       using S = std::remove_pointer_t<decltype(sp)>;
       const int64_t rows = (int64_t)d.geo.ny * d.geo.nz;
-      if (waves_by_node(t, L::Q, d.geo.nx)) {
+      if (waves_by_node(t, L::Q, d.geo.nx, rows)) {
         const unsigned blocks = (unsigned)(((int64_t)d.geo.N + WV_THREADS - 1) / WV_THREADS);
         hipLaunchKernelGGL((waves_node_kernel<L, S>), dim3(blocks), dim3(WV_THREADS), 0, s,
                            static_cast<S *>(d.fout), geom_of(d), t, base);

@@ -28,7 +28,8 @@ inline int64_t waves_blocks(int nx, int64_t rows) {
 // cheaper by node (us a start, by row / by node, D3Q27 FP64 of 2 million nodes: 3 columns 185
 // waves 7985 / 1864; 8 columns 4 waves 661 / 103; 32 columns 185 waves 853 / 1869, 20 waves
 // 462 / 261; 128 columns 20 waves 180 / 270, 4 waves 140 / 104).
-inline bool waves_by_node(const WaveTable &t, int Q, int nx) {
+inline bool waves_by_node(const WaveTable &t, int Q, int nx, int64_t rows) {
+  if (waves_blocks(nx, rows) * WV_THREADS >= (int64_t(1) << 32)) return true;
   const double chunk = 25.0 * Q + 2.0 * Q * t.ngroups + 2.0 * t.nwaves + 8.0 * t.longest;
   return (nx + WV_X - 1) / WV_X * chunk > 1.3 * nx * t.nwaves;
 }

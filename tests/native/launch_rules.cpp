@@ -8,12 +8,13 @@
 int main() {
   char what[32];
   while (std::scanf("%31s", what) == 1) {
-    if (!std::strcmp(what, "waves_by_node")) {  // nwaves ngroups longest Q nx
+    if (!std::strcmp(what, "waves_by_node")) {  // nwaves ngroups longest Q nx rows
       lbm::WaveTable t{};
       int Q, nx;
-      if (std::scanf("%d %d %d %d %d", &t.nwaves, &t.ngroups, &t.longest, &Q, &nx) != 5)
+      long long rows;
+      if (std::scanf("%d %d %d %d %d %lld", &t.nwaves, &t.ngroups, &t.longest, &Q, &nx, &rows) != 6)
         return 1;
-      std::printf("%d\n", (int)lbm::waves_by_node(t, Q, nx));
+      std::printf("%d\n", (int)lbm::waves_by_node(t, Q, nx, rows));
     } else {
       return 1;
     }

@@ -1,5 +1,5 @@
 """lbm_set_waves where a node sums its own waves (narrow rows, few waves) and where its row's
-are summed, against the sum as written."""
+are summed, against the sum as written; and rows whose blocks would pass the largest launch."""
 import math
 
 import numpy as np
@@ -12,7 +12,7 @@ pytestmark = [pytest.mark.gpu,
               pytest.mark.skipif(not gpu_available(), reason="needs a HIP device")]
 
 
-def _check(lat, shape, nw, solid=None):
+def _check(lat, shape, nw, nodes=None, solid=None, storage="f64"):
     from paper_2212_07494_amd import lbm as L
     L.load()
     nx, ny, nz = shape
@@ -22,7 +22,7 @@ def _check(lat, shape, nw, solid=None):
     k[0] = (nx // 2, ny // 2, nz // 2)
     phase = rng.uniform(-7.0, 7.0, size=nw)
     amp = (rng.normal(size=(nw, w.size)) + 1j * rng.normal(size=(nw, w.size))) * 1e-3
-    n = np.arange(nx * ny * nz)
+    n = np.arange(nx * ny * nz) if nodes is None else np.asarray(nodes)
     c = (n % nx, (n // nx) % ny, n // (nx * ny))
     want = np.repeat(w[:, None], n.size, axis=1)
     for kw, ph, a in zip(k.astype(np.int64), phase, amp):
@@ -30,9 +30,11 @@ def _check(lat, shape, nw, solid=None):
         want += np.outer(a.real, np.cos(th)) - np.outer(a.imag, np.sin(th))
     # each wave's angle and factors to a few units of roundoff on either side, and the sums'
     tol = 2.0 ** -53 * (40 * np.abs(amp).sum() / w.size * 4 + nw * np.abs(want).max())
-    with L.Lattice(lat, "smrt", "f64", shape, (0, 0, 0), (0.8, 1.0, 1.0), solid=solid) as lt:
+    if storage == "f16s":  # and a deviation's rounding to binary16
+        tol += 2.0 ** -11 * np.abs(want - w[:, None]).max()
+    with L.Lattice(lat, "smrt", storage, shape, (0, 0, 0), (0.8, 1.0, 1.0), solid=solid) as lt:
         lt.set_waves(k, phase, amp)
-        got = lt.populations()
+        got = lt.populations(nodes) + (w[:, None] if storage == "f16s" else 0)
         live = slice(None) if solid is None else solid == 0
         np.testing.assert_allclose(got[:, live], want[:, live], rtol=0, atol=tol)
 
@@ -50,3 +52,10 @@ def test_solid_nodes_by_node():
     shape = (7, 30, 4)
     solid = (np.random.default_rng(2).random(7 * 30 * 4) < 0.1).astype(np.uint8)
     _check("D3Q19", shape, 5, solid=solid)
+
+
+def test_rows_beyond_the_largest_launch():
+    """8192^2 rows of one node: four rows a workgroup of 256 threads would be 2^32 threads."""
+    n = 8192
+    nodes = np.array([0, 1, 255, 256, n, n * n // 2 + 3, n * n - n, n * n - 2, n * n - 1])
+    _check("D3Q19", (1, n, n), 3, nodes=nodes, storage="f16s")

@@ -26,11 +26,13 @@ def ask(tmp_path_factory):
     return run
 
 
-# nwaves, groups, longest group, Q, nx
+# nwaves, groups, longest group, Q, nx, rows
 @pytest.mark.parametrize("query,by_node", [
-    ((1, 1, 1, 27, 1), 1), ((185, 1, 185, 27, 1), 1),
-    ((9, 5, 4, 19, 16), 1), ((185, 9, 42, 27, 128), 0),
-    ((185, 9, 42, 27, 32), 0), ((1, 1, 1, 27, 128), 1),
-    ((0, 0, 0, 9, 64), 1)])
+    ((1, 1, 1, 27, 1, 10 ** 6), 1), ((185, 1, 185, 27, 1, 10 ** 6), 1),
+    ((9, 5, 4, 19, 16, 62500), 1), ((185, 9, 42, 27, 128, 16384), 0),
+    ((185, 9, 42, 27, 32, 62500), 0), ((1, 1, 1, 27, 128, 16384), 1),
+    ((0, 0, 0, 9, 64, 32), 1),
+    # the rows' launch would pass 2^32 threads: 2^26 rows
+    ((10 ** 4, 16, 700, 39, 31, 1 << 26), 1), ((10 ** 4, 16, 700, 39, 31, 1 << 25), 0)])
 def test_waves_by_node(ask, query, by_node):
     assert ask([("waves_by_node", *query)]) == [[by_node]]
