@@ -183,9 +183,7 @@ struct lbm_batch {
     b.tiles = tiles_d;
     b.active = active_d;
     b.ntiles = ntiles;
-    // blocks_per_cu 0: one workgroup per tile (a multiple of the XCD count, so the
-    // XCD-contiguous tile walk applies); else a persistent grid walking the table
-    b.grid = tune.blocks_per_cu ? tune.blocks_per_cu * ncu : (ntiles + 7) / 8 * 8;
+    b.grid = lbm::batch_grid(tune.blocks_per_cu, ncu, ntiles);
     b.shift = shift;
     b.urec = urec;
     b.uchk = uchk;
@@ -345,6 +343,7 @@ int build_multi(lbm_batch *b) {
     int64_t n = 0;
     for (const auto &m : b->dom)
       n += (int64_t)lbm::multi_columns(m.nx, K) * ((m.ny + oy - 1) / oy);
+    if (n * lbm::MULTI_THREADS >= lbm::MAX_THREADS) continue;
     const double cost = lbm::multi_cost(n, oy, K, b->ncu);
     if (rows && cost >= best) continue;
     best = cost;
@@ -357,7 +356,7 @@ int build_multi(lbm_batch *b) {
     for (int d = 0; d < b->ndom; ++d) {
       const lbm::BatchDom &m = b->dom[d];
       const int ntx = lbm::multi_columns(m.nx, K), nty = (m.ny + rows - 1) / rows;
-      const int ox = (m.nx + ntx - 1) / ntx, oy = (m.ny + nty - 1) / nty;
+      const int ox = m.nx / ntx + (m.nx % ntx != 0), oy = (m.ny + nty - 1) / nty;
       tallest = std::max(tallest, oy);
       for (int y0 = 0; y0 < m.ny; y0 += oy)
         for (int x0 = 0; x0 < m.nx; x0 += ox)

@@ -70,57 +70,6 @@ hipError_t by_collision(const BatchLaunch &b, int k, hipStream_t s) {
 
 }  // namespace
 
-// Steps, columns and rows of the tiles.  A launch whose tiles each find a compute unit of
-// their own lasts as long as one tile, whose stages take their rows in passes of the
-// workgroup's wavefronts: about six rows' worth of latency a pass besides the rows themselves,
-// after 22 for the launch.  There rows of 32 columns, two to a wavefront, halve the passes, and
-// the idle units pay for the wider margins (us a step, 64 against 32 columns: 64 x 32 BGK FP64
-// 1.80 / 1.58, 50 x 200 SMRT FP64 1.61 / 1.47, 128^2 FP64 1.57 / 1.46, 256^2 FP64 2.07 / 1.94);
-// and more steps a launch, where their rows still make one pass.  Launches with more tiles than
-// units are bound by the rows (multi_cost).
-MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu) {
-  MultiPlan p{};
-  // a plane's byte offsets are 32-bit in the kernel
-  if (ncu < 1 || (uint64_t)nx * ny * elem >= (1ull << 32)) return p;
-  constexpr int WAVES = MULTI_THREADS / 64;
-  const int few = multi_steps(ny, wy);
-  double best = 0;
-  auto consider = [&](int K, int wx, bool single) {
-    const int rpw = 64 / wx, ntx = multi_columns(nx, K, wx);
-    for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem, wx) <= (size_t)lds_cu; ++oy) {
-      const int nty = (ny + oy - 1) / oy;
-      const int64_t tiles = (int64_t)ntx * nty;
-      if (single != (tiles <= ncu)) continue;
-      double cost = multi_cost(tiles, oy, K, ncu);
-      if (single) {
-        cost = 22;
-        for (int s = 0; s < K; ++s) {
-          const int rows = (oy + 2 * s + rpw - 1) / rpw;  // of the last stage first
-          cost += 6 * ((rows + WAVES - 1) / WAVES) + rows;
-        }
-        cost /= K;
-      }
-      if (p.K && cost >= best) continue;
-      best = cost;
-      p.K = K;
-      p.wx = wx;
-      p.ntx = ntx;
-      p.oy = oy;
-      p.nty = nty;
-    }
-  };
-  if (few) {
-    consider(few, MULTI_W, true);
-    consider(few, 32, true);
-    if (wy || ny >= 2 * MULTI_STEPS_MAX) consider(MULTI_STEPS_MAX, 32, true);
-    if (!p.K) consider(few, MULTI_W, false);
-  }
-  if (!p.K) return p;
-  p.ox = (nx + p.ntx - 1) / p.ntx;
-  p.lds = (unsigned)multi_lds(p.oy, p.K, elem, p.wx);
-  return p;
-}
-
 hipError_t multi_step_d2q9(const LaunchDesc &d, const MultiPlan &p, int k, const double *gs,
                            hipStream_t s) {
   if (k < 3 || k > p.K || k % 2 == 0) return hipErrorInvalidValue;

@@ -66,45 +66,6 @@ struct LaunchDesc {
   int gs_j;
 };
 
-// Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
-// tile, steps of a launch (and of one on the smallest lattices), threads of a workgroup, and
-// the most rows a plan lets a tile own.
-constexpr int MULTI_W = 64;
-constexpr int MULTI_STEPS = 5, MULTI_STEPS_MAX = 7;
-constexpr int MULTI_THREADS = 512;
-constexpr int MULTI_ROWS = 27;
-
-// Launch of several steps in one pass over a two-dimensional lattice (lbm_multistep.h): K
-// steps (odd, at least 3; 0: no such plan), tiles of ox x oy nodes in an ntx x nty grid,
-// workgroups with `lds` bytes of LDS.
-struct MultiPlan {
-  int K, wx, ox, oy, ntx, nty;  // wx: columns of a wavefront's row (64 or 32)
-  unsigned lds;
-};
-
-// The tiles a lattice's nx columns are split into, one beside the other, for K steps a
-// launch: one of up to wx columns that wraps (or bounces) inside itself, else tiles that
-// leave room for K - 1 columns more on each side.
-inline int multi_columns(int nx, int K, int wx = MULTI_W) {
-  const int room = nx <= wx ? nx : wx - 2 * (K - 1);
-  return (nx + room - 1) / room;
-}
-// LDS of a tile of oy rows, and the steps of a launch on a lattice of ny rows (0: none; a
-// periodic lattice wraps once, and one of few rows would mostly compute its margins).
-inline size_t multi_lds(int oy, int K, size_t elem, int wx = MULTI_W) {
-  return (size_t)(oy + 2 * (K - 1)) * wx * 9 * elem;
-}
-inline int multi_steps(int ny, bool wy) { return wy || ny >= 12 ? MULTI_STEPS : (ny >= 3 ? 3 : 0); }
-// Relative time of a launch of `tiles` tiles of oy rows: the compute units take them in
-// turn, and a tile costs the rows of its K stages and about five more for its start and end.
-// The fastest heights sit where the tiles just fill the compute units once, twice, ...:
-// 512^2 FP32-shifted (10 columns) 22 rows, 240 tiles, 2.95 us a step against 4.08 at 20 rows,
-// 260 tiles; 900^2 (17 columns) 20 rows, 765 tiles, 6.1 against 7.1 at 18 rows.  MULTI_ROWS
-// keeps two workgroups a compute unit in FP32 (28 rows at 2048^2: 36 us a step, 26: 26).
-inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
-  return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
-}
-
 // One launch of the batched engine's persistent kernels.
 struct BatchLaunch {
   int coll, storage, variant;
@@ -182,7 +143,6 @@ hipError_t decide_domains(const int *tile_begin, const int *tile_end, const doub
 hipError_t add_domain_steps(const int *active, void *state, int ndom, int64_t n, hipStream_t s);
 
 // lbm_d2q9_multi.h (part of lbm_d2q9.hip)
-MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu);
 hipError_t multi_step_d2q9(const LaunchDesc &, const MultiPlan &, int k, const double *gs,
                            hipStream_t);
 hipError_t batch_multi_d2q9(const BatchLaunch &, int k, hipStream_t);

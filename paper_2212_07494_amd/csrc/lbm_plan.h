@@ -1,9 +1,103 @@
 // Rules that choose a launch by sizes (host code without HIP): which kernel, which tiles.
 #pragma once
 
+#include <cstddef>
 #include <cstdint>
 
 namespace lbm {
+
+// A launch holds fewer than 2^32 threads.
+constexpr int64_t MAX_THREADS = int64_t(1) << 32;
+
+// Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
+// tile, steps of a launch (and of one on the smallest lattices), threads of a workgroup, and
+// the most rows a plan lets a tile own.
+constexpr int MULTI_W = 64;
+constexpr int MULTI_STEPS = 5, MULTI_STEPS_MAX = 7;
+constexpr int MULTI_THREADS = 512;
+constexpr int MULTI_ROWS = 27;
+
+// Launch of several steps in one pass over a two-dimensional lattice (lbm_multistep.h): K
+// steps (odd, at least 3; 0: no such plan), tiles of ox x oy nodes in an ntx x nty grid,
+// workgroups with `lds` bytes of LDS.
+struct MultiPlan {
+  int K, wx, ox, oy, ntx, nty;  // wx: columns of a wavefront's row (64 or 32)
+  unsigned lds;
+};
+
+// The tiles a lattice's nx columns are split into, one beside the other, for K steps a
+// launch: one of up to wx columns that wraps (or bounces) inside itself, else tiles that
+// leave room for K - 1 columns more on each side.
+inline int multi_columns(int nx, int K, int wx = MULTI_W) {
+  const int room = nx <= wx ? nx : wx - 2 * (K - 1);
+  return nx / room + (nx % room != 0);
+}
+// LDS of a tile of oy rows, and the steps of a launch on a lattice of ny rows (0: none; a
+// periodic lattice wraps once, and one of few rows would mostly compute its margins).
+inline size_t multi_lds(int oy, int K, size_t elem, int wx = MULTI_W) {
+  return (size_t)(oy + 2 * (K - 1)) * wx * 9 * elem;
+}
+inline int multi_steps(int ny, bool wy) { return wy || ny >= 12 ? MULTI_STEPS : (ny >= 3 ? 3 : 0); }
+// Relative time of a launch of `tiles` tiles of oy rows: the compute units take them in
+// turn, and a tile costs the rows of its K stages and about five more for its start and end.
+// The fastest heights sit where the tiles just fill the compute units once, twice, ...:
+// 512^2 FP32-shifted (10 columns) 22 rows, 240 tiles, 2.95 us a step against 4.08 at 20 rows,
+// 260 tiles; 900^2 (17 columns) 20 rows, 765 tiles, 6.1 against 7.1 at 18 rows.  MULTI_ROWS
+// keeps two workgroups a compute unit in FP32 (28 rows at 2048^2: 36 us a step, 26: 26).
+inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
+  return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
+}
+
+// Steps, columns and rows of the tiles.  A launch whose tiles each find a compute unit of
+// their own lasts as long as one tile, whose stages take their rows in passes of the
+// workgroup's wavefronts: about six rows' worth of latency a pass besides the rows themselves,
+// after 22 for the launch.  There rows of 32 columns, two to a wavefront, halve the passes, and
+// the idle units pay for the wider margins (us a step, 64 against 32 columns: 64 x 32 BGK FP64
+// 1.80 / 1.58, 50 x 200 SMRT FP64 1.61 / 1.47, 128^2 FP64 1.57 / 1.46, 256^2 FP64 2.07 / 1.94);
+// and more steps a launch, where their rows still make one pass.  Launches with more tiles than
+// units are bound by the rows (multi_cost).
+inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu) {
+  MultiPlan p{};
+  // a plane's byte offsets are 32-bit in the kernel
+  if (ncu < 1 || (uint64_t)nx * ny * elem >= (1ull << 32)) return p;
+  constexpr int WAVES = MULTI_THREADS / 64;
+  const int few = multi_steps(ny, wy);
+  double best = 0;
+  auto consider = [&](int K, int wx, bool single) {
+    const int rpw = 64 / wx, ntx = multi_columns(nx, K, wx);
+    for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem, wx) <= (size_t)lds_cu; ++oy) {
+      const int nty = (ny + oy - 1) / oy;
+      const int64_t tiles = (int64_t)ntx * nty;
+      if (single != (tiles <= ncu) || tiles * MULTI_THREADS >= MAX_THREADS) continue;
+      double cost = multi_cost(tiles, oy, K, ncu);
+      if (single) {
+        cost = 22;
+        for (int s = 0; s < K; ++s) {
+          const int rows = (oy + 2 * s + rpw - 1) / rpw;  // of the last stage first
+          cost += 6 * ((rows + WAVES - 1) / WAVES) + rows;
+        }
+        cost /= K;
+      }
+      if (p.K && cost >= best) continue;
+      best = cost;
+      p.K = K;
+      p.wx = wx;
+      p.ntx = ntx;
+      p.oy = oy;
+      p.nty = nty;
+    }
+  };
+  if (few) {
+    consider(few, MULTI_W, true);
+    consider(few, 32, true);
+    if (wy || ny >= 2 * MULTI_STEPS_MAX) consider(MULTI_STEPS_MAX, 32, true);
+    if (!p.K) consider(few, MULTI_W, false);
+  }
+  if (!p.K) return p;
+  p.ox = nx / p.ntx + (nx % p.ntx != 0);
+  p.lds = (unsigned)multi_lds(p.oy, p.K, elem, p.wx);
+  return p;
+}
 
 // Fourier waves for waves_kernel (device arrays), sorted into groups of one k_x: group g's
 // waves are [group_start[g], group_start[g + 1]), `longest` of them at most, and its wavenumber
@@ -29,9 +123,18 @@ inline int64_t waves_blocks(int nx, int64_t rows) {
 // waves 7985 / 1864; 8 columns 4 waves 661 / 103; 32 columns 185 waves 853 / 1869, 20 waves
 // 462 / 261; 128 columns 20 waves 180 / 270, 4 waves 140 / 104).
 inline bool waves_by_node(const WaveTable &t, int Q, int nx, int64_t rows) {
-  if (waves_blocks(nx, rows) * WV_THREADS >= (int64_t(1) << 32)) return true;
+  if (waves_blocks(nx, rows) * WV_THREADS >= MAX_THREADS) return true;
   const double chunk = 25.0 * Q + 2.0 * Q * t.ngroups + 2.0 * t.nwaves + 8.0 * t.longest;
   return (nx + WV_X - 1) / WV_X * chunk > 1.3 * nx * t.nwaves;
+}
+
+// Workgroups of 256 threads of a batch's single steps, which walk its tiles: blocks_per_cu a
+// compute unit, or (0) one a tile (a multiple of the XCD count, so that the XCD-contiguous walk
+// applies) as far as a launch goes.
+inline int batch_grid(int blocks_per_cu, int ncu, int ntiles) {
+  if (blocks_per_cu) return blocks_per_cu * ncu;
+  const int64_t most = MAX_THREADS / 256 - 8, grid = ((int64_t)ntiles + 7) / 8 * 8;
+  return (int)(grid < most ? grid : most);
 }
 
 }  // namespace lbm

@@ -15,6 +15,15 @@ int main() {
       if (std::scanf("%d %d %d %d %d %lld", &t.nwaves, &t.ngroups, &t.longest, &Q, &nx, &rows) != 6)
         return 1;
       std::printf("%d\n", (int)lbm::waves_by_node(t, Q, nx, rows));
+    } else if (!std::strcmp(what, "multi_plan")) {  // nx ny wy bytes lds ncu
+      int nx, ny, wy, elem, lds, ncu;
+      if (std::scanf("%d %d %d %d %d %d", &nx, &ny, &wy, &elem, &lds, &ncu) != 6) return 1;
+      const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem, lds, ncu);
+      std::printf("%d %d %d %d %d %d %u\n", p.K, p.wx, p.ox, p.oy, p.ntx, p.nty, p.lds);
+    } else if (!std::strcmp(what, "batch_grid")) {  // blocks_per_cu ncu ntiles
+      int bpc, ncu, ntiles;
+      if (std::scanf("%d %d %d", &bpc, &ncu, &ntiles) != 3) return 1;
+      std::printf("%d\n", lbm::batch_grid(bpc, ncu, ntiles));
     } else {
       return 1;
     }

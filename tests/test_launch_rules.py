@@ -36,3 +36,33 @@ def ask(tmp_path_factory):
     ((10 ** 4, 16, 700, 39, 31, 1 << 26), 1), ((10 ** 4, 16, 700, 39, 31, 1 << 25), 0)])
 def test_waves_by_node(ask, query, by_node):
     assert ask([("waves_by_node", *query)]) == [[by_node]]
+
+
+LDS, NCU = 160 * 1024, 256
+
+
+def test_plan_covers_the_lattice_within_a_launch(ask):
+    """Tiles cover every node once and none is empty, margins leave room in a tile's columns,
+    the LDS holds it, and a launch stays below 2^32 threads (512 a tile)."""
+    sizes = [1, 2, 3, 5, 11, 12, 14, 27, 28, 32, 33, 53, 57, 64, 65, 113, 200, 1000, 65535]
+    cases = [(nx, ny, wy, elem) for nx in sizes + [1 << 20, 5 * 10 ** 8, 10 ** 9, 2 ** 31 - 1] for ny in sizes
+             for wy in (0, 1) for elem in (2, 4, 8) if nx * ny < 2 ** 31]
+    got = ask([("multi_plan", *c, LDS, NCU) for c in cases])
+    assert len(got) == len(cases)
+    for (nx, ny, wy, elem), (K, wx, ox, oy, ntx, nty, lds) in zip(cases, got):
+        if not K:
+            continue
+        what = (nx, ny, wy, elem)
+        assert K in (3, 5, 7) and (wy or ny >= 2 * K - 2 or K == 3 and ny >= 3), what
+        assert (ntx - 1) * ox < nx <= ntx * ox and (nty - 1) * oy < ny <= nty * oy, what
+        assert ntx == 1 and nx <= wx or ox + 2 * (K - 1) <= wx, what
+        assert lds == (oy + 2 * (K - 1)) * wx * 9 * elem <= LDS, what
+        assert ntx * nty * 512 < 2 ** 32, what
+
+
+@pytest.mark.parametrize("query,grid", [
+    ((8, 256, 10 ** 6), 2048), ((0, 256, 1), 8), ((0, 256, 17), 24),
+    ((0, 256, 2 ** 24 - 9), 2 ** 24 - 8), ((0, 256, 2 ** 24), 2 ** 24 - 8),
+    ((0, 256, 2 ** 31 - 1), 2 ** 24 - 8)])
+def test_batch_grid(ask, query, grid):
+    assert ask([("batch_grid", *query)]) == [[grid]]
