@@ -45,10 +45,10 @@ struct BatchMultiTile {
 // This lane's node of a tile; false if it lies beyond the domain.
 __device__ __forceinline__ bool tile_xy(const BatchTile &t, const BatchDom &dm, int &x, int &y) {
   if (dm.tbx_log2 < 0) {
-    const int r = t.x0 + (int)threadIdx.x;
-    if (r >= dm.nx * dm.ny) return false;
-    y = r / dm.nx;
-    x = r - y * dm.nx;
+    const uint32_t r = (uint32_t)t.x0 + threadIdx.x;  // may pass 2^31
+    if (r >= (uint32_t)(dm.nx * dm.ny)) return false;
+    y = (int)r / dm.nx;
+    x = (int)r - y * dm.nx;
     return true;
   }
   x = t.x0 + (threadIdx.x & ((1 << dm.tbx_log2) - 1));
@@ -61,8 +61,8 @@ template <class S>
 __device__ __forceinline__ bool tile_fast(const BatchTile &t, const BatchDom &dm,
                                           const Geom &geo) {
   if (dm.tbx_log2 < 0) {
-    const int last = min(t.x0 + 255, dm.nx * dm.ny - 1);
-    return fast_block<S>(geo, 0, dm.nx - 1, t.x0 / dm.nx, last / dm.nx, t.z);
+    const uint32_t last = min((uint32_t)t.x0 + 255, (uint32_t)(dm.nx * dm.ny) - 1);
+    return fast_block<S>(geo, 0, dm.nx - 1, t.x0 / dm.nx, (int)last / dm.nx, t.z);
   }
   return fast_block<S>(geo, t.x0, t.x0 + (1 << dm.tbx_log2) - 1, t.y0,
                        t.y0 + (256 >> dm.tbx_log2) - 1, t.z);

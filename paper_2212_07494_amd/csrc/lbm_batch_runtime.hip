@@ -240,14 +240,16 @@ int build_tiles(lbm_batch *b) {
       // the layer, every lane busy except in a layer's last tile
       m.tbx_log2 = -1;
       for (int z = 0; z < m.nz; ++z)
-        for (int r0 = 0; r0 < m.nx * m.ny; r0 += 256) tiles.push_back({d, r0, 0, z});
+        lbm::each_piece((int64_t)m.nx * m.ny, 256,
+                        [&](int r0, int) { tiles.push_back({d, r0, 0, z}); });
     } else {
       const int tbx = tile_width(b->tune.tile_bx, m.nx);
       const int tby = 256 / tbx;
       m.tbx_log2 = log2i(tbx);
       for (int z = 0; z < m.nz; ++z)
-        for (int y0 = 0; y0 < m.ny; y0 += tby)
-          for (int x0 = 0; x0 < m.nx; x0 += tbx) tiles.push_back({d, x0, y0, z});
+        lbm::each_piece(m.ny, tby, [&](int y0, int) {
+          lbm::each_piece(m.nx, tbx, [&](int x0, int) { tiles.push_back({d, x0, y0, z}); });
+        });
     }
     m.tile_end = (int)tiles.size();
     tb[d] = m.tile_begin;
@@ -342,7 +344,7 @@ int build_multi(lbm_batch *b) {
   for (int oy = 1; oy <= lbm::MULTI_ROWS && lbm::multi_lds(oy, K, sb) <= (size_t)b->lds_cu; ++oy) {
     int64_t n = 0;
     for (const auto &m : b->dom)
-      n += (int64_t)lbm::multi_columns(m.nx, K) * ((m.ny + oy - 1) / oy);
+      n += (int64_t)lbm::multi_columns(m.nx, K) * lbm::ceil_div(m.ny, oy);
     if (n * lbm::MULTI_THREADS >= lbm::MAX_THREADS) continue;
     const double cost = lbm::multi_cost(n, oy, K, b->ncu);
     if (rows && cost >= best) continue;
@@ -355,12 +357,12 @@ int build_multi(lbm_batch *b) {
   try {
     for (int d = 0; d < b->ndom; ++d) {
       const lbm::BatchDom &m = b->dom[d];
-      const int ntx = lbm::multi_columns(m.nx, K), nty = (m.ny + rows - 1) / rows;
-      const int ox = m.nx / ntx + (m.nx % ntx != 0), oy = (m.ny + nty - 1) / nty;
+      const int ntx = lbm::multi_columns(m.nx, K), nty = lbm::ceil_div(m.ny, rows);
+      const int ox = lbm::ceil_div(m.nx, ntx), oy = lbm::ceil_div(m.ny, nty);
       tallest = std::max(tallest, oy);
-      for (int y0 = 0; y0 < m.ny; y0 += oy)
-        for (int x0 = 0; x0 < m.nx; x0 += ox)
-          tiles.push_back({d, x0, y0, std::min(ox, m.nx - x0), std::min(oy, m.ny - y0)});
+      lbm::each_piece(m.ny, oy, [&](int y0, int h) {
+        lbm::each_piece(m.nx, ox, [&](int x0, int w) { tiles.push_back({d, x0, y0, w, h}); });
+      });
     }
   } catch (const std::bad_alloc &) {
     return set_error(LBM_ENOMEM, "host memory for the tiles");

@@ -9,6 +9,15 @@ namespace lbm {
 // A launch holds fewer than 2^32 threads.
 constexpr int64_t MAX_THREADS = int64_t(1) << 32;
 
+// n / d rounded up, for n up to 2^31 - 1.
+inline int ceil_div(int n, int d) { return n / d + (n % d != 0); }
+
+// f(start, length) of the pieces of `size` that n < 2^31 is cut into (the last may be shorter).
+template <class F>
+void each_piece(int64_t n, int size, F f) {
+  for (int64_t i = 0; i < n; i += size) f((int)i, (int)(n - i < size ? n - i : size));
+}
+
 // Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
 // tile, steps of a launch (and of one on the smallest lattices), threads of a workgroup, and
 // the most rows a plan lets a tile own.
@@ -30,7 +39,7 @@ struct MultiPlan {
 // leave room for K - 1 columns more on each side.
 inline int multi_columns(int nx, int K, int wx = MULTI_W) {
   const int room = nx <= wx ? nx : wx - 2 * (K - 1);
-  return nx / room + (nx % room != 0);
+  return ceil_div(nx, room);
 }
 // LDS of a tile of oy rows, and the steps of a launch on a lattice of ny rows (0: none; a
 // periodic lattice wraps once, and one of few rows would mostly compute its margins).
@@ -66,7 +75,7 @@ inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, in
   auto consider = [&](int K, int wx, bool single) {
     const int rpw = 64 / wx, ntx = multi_columns(nx, K, wx);
     for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem, wx) <= (size_t)lds_cu; ++oy) {
-      const int nty = (ny + oy - 1) / oy;
+      const int nty = ceil_div(ny, oy);
       const int64_t tiles = (int64_t)ntx * nty;
       if (single != (tiles <= ncu) || tiles * MULTI_THREADS >= MAX_THREADS) continue;
       double cost = multi_cost(tiles, oy, K, ncu);
@@ -94,7 +103,7 @@ inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, in
     if (!p.K) consider(few, MULTI_W, false);
   }
   if (!p.K) return p;
-  p.ox = nx / p.ntx + (nx % p.ntx != 0);
+  p.ox = ceil_div(nx, p.ntx);
   p.lds = (unsigned)multi_lds(p.oy, p.K, elem, p.wx);
   return p;
 }

@@ -20,6 +20,16 @@ int main() {
       if (std::scanf("%d %d %d %d %d %d", &nx, &ny, &wy, &elem, &lds, &ncu) != 6) return 1;
       const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem, lds, ncu);
       std::printf("%d %d %d %d %d %d %u\n", p.K, p.wx, p.ox, p.oy, p.ntx, p.nty, p.lds);
+    } else if (!std::strcmp(what, "pieces")) {  // n size -> count, last start, last length
+      long long n;
+      int size, count = 0, start = 0, length = 0;
+      if (std::scanf("%lld %d", &n, &size) != 2) return 1;
+      lbm::each_piece(n, size, [&](int i, int len) {
+        ++count;
+        start = i;
+        length = len;
+      });
+      std::printf("%d %d %d %d\n", count, start, length, n ? lbm::ceil_div((int)n, size) : 0);
     } else if (!std::strcmp(what, "batch_grid")) {  // blocks_per_cu ncu ntiles
       int bpc, ncu, ntiles;
       if (std::scanf("%d %d %d", &bpc, &ncu, &ntiles) != 3) return 1;

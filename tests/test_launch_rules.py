@@ -66,3 +66,12 @@ def test_plan_covers_the_lattice_within_a_launch(ask):
     ((0, 256, 2 ** 31 - 1), 2 ** 24 - 8)])
 def test_batch_grid(ask, query, grid):
     assert ask([("batch_grid", *query)]) == [[grid]]
+
+
+@pytest.mark.parametrize("n", [0, 1, 255, 256, 257, 2 ** 31 - 257, 2 ** 31 - 256, 2 ** 31 - 255,
+                               2 ** 31 - 1])
+def test_pieces(ask, n):
+    """Tiles of up to 256 nodes of the largest domains: no sum passes 2^31."""
+    count = -(-n // 256)
+    start = max(0, count - 1) * 256
+    assert ask([("pieces", n, 256)]) == [[count, start, n - start, count]]
