@@ -101,7 +101,8 @@ struct lbm_batch {
   size_t scratch_bytes = 0;
   size_t bytes = 0;
   lbm_batch_tuning tune{0, 8, 1};  // set by size at init (default_tuning)
-  int ncu = 256, lds_cu = 0;
+  int ncu = 256;
+  size_t lds = 0;  // bytes a workgroup may take
   // several steps a launch (D2Q9): steps (0: none), tiles and their LDS
   int multi_K = 0, nmulti = 0;
   unsigned multi_lds = 0;
@@ -341,7 +342,7 @@ int build_multi(lbm_batch *b) {
   if (!K) return LBM_OK;
   int rows = 0;
   double best = 0;
-  for (int oy = 1; oy <= lbm::MULTI_ROWS && lbm::multi_lds(oy, K, sb) <= (size_t)b->lds_cu; ++oy) {
+  for (int oy = 1; oy <= lbm::MULTI_ROWS && lbm::multi_lds(oy, K, sb) <= b->lds; ++oy) {
     int64_t n = 0;
     for (const auto &m : b->dom)
       n += (int64_t)lbm::multi_columns(m.nx, K) * lbm::ceil_div(m.ny, oy);
@@ -453,9 +454,12 @@ int lbm_batch_init(const lbm_domain *domains, int32_t ndom, int32_t lattice, int
   hipDeviceProp_t prop;
   if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)
     b->ncu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
-  if (hipDeviceGetAttribute(&b->lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) !=
-      hipSuccess)
-    b->lds_cu = 0;
+  int lds_cu = 0, lds_block = 0;
+  if (hipDeviceGetAttribute(&lds_cu, hipDeviceAttributeMaxSharedMemoryPerMultiprocessor, dev) ==
+          hipSuccess &&
+      hipDeviceGetAttribute(&lds_block, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) ==
+          hipSuccess)
+    b->lds = lbm::workgroup_lds(lds_cu, lds_block);
 
   // pack the domains
   const size_t ab = arith_bytes(storage);

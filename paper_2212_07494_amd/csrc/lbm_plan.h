@@ -18,6 +18,13 @@ void each_piece(int64_t n, int size, F f) {
   for (int64_t i = 0; i < n; i += size) f((int)i, (int)(n - i < size ? n - i : size));
 }
 
+// LDS bytes a workgroup may take for its data: what a compute unit has, and no more than one
+// workgroup is allowed.
+inline size_t workgroup_lds(int lds_cu, int lds_block) {
+  const int least = lds_cu < lds_block ? lds_cu : lds_block;
+  return least > 0 ? (size_t)least : 0;
+}
+
 // Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
 // tile, steps of a launch (and of one on the smallest lattices), threads of a workgroup, and
 // the most rows a plan lets a tile own.
@@ -65,7 +72,7 @@ inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
 // 1.80 / 1.58, 50 x 200 SMRT FP64 1.61 / 1.47, 128^2 FP64 1.57 / 1.46, 256^2 FP64 2.07 / 1.94);
 // and more steps a launch, where their rows still make one pass.  Launches with more tiles than
 // units are bound by the rows (multi_cost).
-inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, int ncu) {
+inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, size_t lds, int ncu) {
   MultiPlan p{};
   // a plane's byte offsets are 32-bit in the kernel
   if (ncu < 1 || (uint64_t)nx * ny * elem >= (1ull << 32)) return p;
@@ -74,7 +81,7 @@ inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, int lds_cu, in
   double best = 0;
   auto consider = [&](int K, int wx, bool single) {
     const int rpw = 64 / wx, ntx = multi_columns(nx, K, wx);
-    for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem, wx) <= (size_t)lds_cu; ++oy) {
+    for (int oy = 1; oy <= MULTI_ROWS && multi_lds(oy, K, elem, wx) <= lds; ++oy) {
       const int nty = ceil_div(ny, oy);
       const int64_t tiles = (int64_t)ntx * nty;
       if (single != (tiles <= ncu) || tiles * MULTI_THREADS >= MAX_THREADS) continue;

@@ -823,7 +823,7 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
   block_shape(p->nx, c->bx, c->by);
   if (c->ops->multi && !p->debug_poison)
     c->multi = lbm::multi_plan(p->nx, p->ny, p->bc[1] == LBM_WALLS, storage_bytes(p->storage),
-                               c->lds_cu, ncu);
+                               lbm::workgroup_lds(c->lds_cu, c->lds_block), ncu);
   const size_t pop_bytes = (size_t)c->Q * (size_t)c->N * storage_bytes(p->storage);
   c->variant = default_variant(pop_bytes);
   const size_t ab = arith_bytes(p->storage);

@@ -15,10 +15,12 @@ int main() {
       if (std::scanf("%d %d %d %d %d %lld", &t.nwaves, &t.ngroups, &t.longest, &Q, &nx, &rows) != 6)
         return 1;
       std::printf("%d\n", (int)lbm::waves_by_node(t, Q, nx, rows));
-    } else if (!std::strcmp(what, "multi_plan")) {  // nx ny wy bytes lds ncu
-      int nx, ny, wy, elem, lds, ncu;
-      if (std::scanf("%d %d %d %d %d %d", &nx, &ny, &wy, &elem, &lds, &ncu) != 6) return 1;
-      const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem, lds, ncu);
+    } else if (!std::strcmp(what, "multi_plan")) {  // nx ny wy bytes lds_cu lds_block ncu
+      int nx, ny, wy, elem, cu, block, ncu;
+      if (std::scanf("%d %d %d %d %d %d %d", &nx, &ny, &wy, &elem, &cu, &block, &ncu) != 7)
+        return 1;
+      const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem,
+                                               lbm::workgroup_lds(cu, block), ncu);
       std::printf("%d %d %d %d %d %d %u\n", p.K, p.wx, p.ox, p.oy, p.ntx, p.nty, p.lds);
     } else if (!std::strcmp(what, "pieces")) {  // n size -> count, last start, last length
       long long n;

@@ -47,7 +47,7 @@ def test_plan_covers_the_lattice_within_a_launch(ask):
     sizes = [1, 2, 3, 5, 11, 12, 14, 27, 28, 32, 33, 53, 57, 64, 65, 113, 200, 1000, 65535]
     cases = [(nx, ny, wy, elem) for nx in sizes + [1 << 20, 5 * 10 ** 8, 10 ** 9, 2 ** 31 - 1] for ny in sizes
              for wy in (0, 1) for elem in (2, 4, 8) if nx * ny < 2 ** 31]
-    got = ask([("multi_plan", *c, LDS, NCU) for c in cases])
+    got = ask([("multi_plan", *c, LDS, LDS, NCU) for c in cases])
     assert len(got) == len(cases)
     for (nx, ny, wy, elem), (K, wx, ox, oy, ntx, nty, lds) in zip(cases, got):
         if not K:
@@ -75,3 +75,11 @@ def test_pieces(ask, n):
     count = -(-n // 256)
     start = max(0, count - 1) * 256
     assert ask([("pieces", n, 256)]) == [[count, start, n - start, count]]
+
+
+@pytest.mark.parametrize("cu,block,most", [(LDS, 64 * 1024, 64 * 1024), (64 * 1024, LDS, 64 * 1024),
+                                           (LDS, 4000, 0), (LDS, 0, 0), (LDS, -1, 0)])
+def test_tiles_fit_a_workgroup(ask, cu, block, most):
+    """The LDS of a tile is what one workgroup may take, not what a compute unit has."""
+    (K, *_, lds), = ask([("multi_plan", 1024, 1024, 0, 8, cu, block, NCU)])
+    assert lds <= most and (K > 0) == (most > 0)
