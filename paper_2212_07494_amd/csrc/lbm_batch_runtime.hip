@@ -87,16 +87,6 @@ struct lbm_batch {
   double *partials = nullptr;
   int *active_d = nullptr, *n_active_d = nullptr;
   lbm::DomState *state_d = nullptr;
-  // Small read-backs: from the ninth on they are written into pinned memory, 20-45 us less
-  // each, of a power of two (domains differ in size).  Giving that memory back costs 220 us.
-  lbm::HostFields fields;
-  int small_reads = 0;
-  double *read_back(size_t n) {
-    if (n > lbm::HostFields::kMost || (small_reads < 8 && ++small_reads)) return nullptr;
-    size_t room = 1u << 16;
-    while (room < n) room *= 2;
-    return fields.get(room);
-  }
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
   size_t bytes = 0;
@@ -295,7 +285,6 @@ void release(lbm_batch *b) {
   (void)hipStreamSynchronize(b->stream);
   b->drop_graph();
   if (b->cap) (void)hipStreamDestroy(b->cap);
-  b->fields.release();
   void *ptrs[] = {b->buf[0], b->buf[1], b->gbuf,     b->urec,         b->uchk,  b->doms_d,
                   b->tiles_d, b->tile_begin_d, b->tile_end_d, b->partials, b->active_d,
                   b->n_active_d, b->state_d, b->scratch, b->multi_d};
@@ -681,11 +670,12 @@ int lbm_batch_moments(lbm_batch *b, int32_t dom, double *rho, double *u) {
   if (!valid(b)) return set_error(LBM_ESTATE, "invalid batch");
   if (dom < 0 || dom >= b->ndom) return set_error(LBM_EINVAL, "domain %d out of range", dom);
   const size_t fld = (size_t)b->dom[dom].N * sizeof(double);
-  if (double *h = b->read_back(fld * (1 + b->D))) {
+  if (double *h = lbm::borrow_pinned(fld * (1 + b->D))) {
     HIP_TRY(b->ops->moments(b->desc(dom), h, h + b->dom[dom].N, b->stream));
     HIP_TRY(hipStreamSynchronize(b->stream));
     if (rho) std::memcpy(rho, h, fld);
     if (u) std::memcpy(u, h + b->dom[dom].N, fld * b->D);
+    lbm::return_pinned(h);
     return LBM_OK;
   }
   int rc = b->need_scratch(fld * (1 + b->D));

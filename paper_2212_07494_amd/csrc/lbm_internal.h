@@ -168,31 +168,17 @@ int sort_waves(int n, int Q, const int32_t *k, const double *phase, const double
                int *longest);
 
 // Pinned host memory that a kernel writes a small read-back's fields into: the two copies to
-// pageable memory of a few kilobytes cost more than the fields.
-struct HostFields {
-  static constexpr size_t kMost = 1u << 20;
-  double *mem = nullptr;
-  size_t bytes = 0;
-  // memory for n bytes, or NULL (too many, or none to be had): copy from the device instead
-  double *get(size_t n) {
-    if (n > kMost) return nullptr;
-    if (n > bytes) {
-      release();
-      if (hipHostMalloc(reinterpret_cast<void **>(&mem), n, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        mem = nullptr;
-        return nullptr;
-      }
-      bytes = n;
-    }
-    return mem;
-  }
-  void release() {
-    if (mem) (void)hipHostFree(mem);
-    mem = nullptr;
-    bytes = 0;
-  }
-};
+// pageable memory of a few kilobytes cost more than the fields (32 x 32 D2Q9: 48 us a read
+// against 17).  Allocating and freeing pinned memory costs more again, so the blocks are the
+// process's: a read borrows one for its duration, at most PINNED_BLOCKS are ever allocated (by
+// the first reads that need them), and they stay until the process ends.
+// borrow_pinned: a block of at least n bytes, or NULL (n too large, all lent, none to be had):
+// then copy from the device.  return_pinned: once nothing can write to it any more; after a
+// failed launch or wait it is kept back for good.  Any thread, any device.
+constexpr size_t PINNED_BYTES = 1u << 20;
+constexpr int PINNED_BLOCKS = 8;
+double *borrow_pinned(size_t n);
+void return_pinned(double *block);
 
 // Error reporting shared by the runtime units (lbm_runtime.hip): records the message
 // for lbm_last_error() and returns status.

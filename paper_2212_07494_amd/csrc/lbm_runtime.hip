@@ -46,6 +46,40 @@ int lbm::set_error(int status, const char *fmt, ...) {
 
 namespace {
 
+std::mutex g_pinned_lock;
+double *g_pinned_idle[lbm::PINNED_BLOCKS];
+int g_pinned_idle_n = 0, g_pinned_made = 0;
+
+}  // namespace
+
+double *lbm::borrow_pinned(size_t n) {
+  if (n > PINNED_BYTES) return nullptr;
+  {
+    std::lock_guard<std::mutex> lock(g_pinned_lock);
+    if (g_pinned_idle_n > 0) return g_pinned_idle[--g_pinned_idle_n];
+    if (g_pinned_made == PINNED_BLOCKS) return nullptr;
+    ++g_pinned_made;
+  }
+  // another thread's stream capture stays valid through the allocation
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  void *block = nullptr;
+  const hipError_t e = hipHostMalloc(&block, PINNED_BYTES, hipHostMallocPortable);
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (e == hipSuccess) return static_cast<double *>(block);
+  (void)hipGetLastError();
+  std::lock_guard<std::mutex> lock(g_pinned_lock);
+  --g_pinned_made;
+  return nullptr;
+}
+
+void lbm::return_pinned(double *block) {
+  std::lock_guard<std::mutex> lock(g_pinned_lock);
+  g_pinned_idle[g_pinned_idle_n++] = block;
+}
+
+namespace {
+
 #define HIP_TRY(expr)                                                                     \
   do {                                                                                    \
     hipError_t e_ = (expr);                                                               \
@@ -219,15 +253,6 @@ struct lbm_ctx {
         if (e) (void)hipGraphExecDestroy(e);
         e = nullptr;
       }
-  }
-  // Small read-backs: from the ninth on they are written into pinned memory, 20-45 us less
-  // each.  Giving that memory back costs 220 us, which a lattice that is read a few times
-  // (32 x 32: closed in 6 us) does not earn.
-  lbm::HostFields fields;
-  int small_reads = 0;
-  double *read_back(size_t n) {
-    if (n > lbm::HostFields::kMost || (small_reads < 8 && ++small_reads)) return nullptr;
-    return fields.get(n);
   }
   void *scratch = nullptr;
   size_t scratch_bytes = 0;
@@ -433,7 +458,6 @@ void release(lbm_ctx *c) {
   c->dfree(c->partials);
   c->dfree(c->mon_dev);
   c->dfree(c->scratch);
-  c->fields.release();
   if (c->mon_host) (void)hipHostFree(c->mon_host);
   if (c->mon_ev) (void)hipEventDestroy(c->mon_ev);
   c->drop_graphs();
@@ -1133,7 +1157,7 @@ int lbm_monitors_get(lbm_ctx *c, lbm_monitors *mon) {
     mode = c->dev_mode;
   } else {
     mode = (c->uprev_time == c->t - 1) ? 4 : 2;
-    host = c->read_back(lbm::MON_SLOTS * sizeof(double));
+    host = lbm::borrow_pinned(lbm::MON_SLOTS * sizeof(double));
     int rc = refresh_monitors(c, mode, host);
     if (rc) return rc;
     c->uprev_time = c->t;
@@ -1144,7 +1168,10 @@ int lbm_monitors_get(lbm_ctx *c, lbm_monitors *mon) {
   if (!host)
     HIP_TRY(hipMemcpyAsync(h, c->mon_dev, sizeof(h), hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
-  if (host) std::memcpy(h, host, sizeof(h));
+  if (host) {
+    std::memcpy(h, host, sizeof(h));
+    lbm::return_pinned(host);
+  }
   c->check_pending = false;  // this record is the latest
   const lbm_monitors m = record_of(h, c->t, mode);
   c->mon = m;
@@ -1157,11 +1184,12 @@ int lbm_moments(lbm_ctx *c, double g_scale, double *rho, double *u) {
   if (!std::isfinite(g_scale)) return fail(LBM_EINVAL, "g_scale is not finite");
   const size_t fld = (size_t)c->N * sizeof(double);
   lbm::LaunchDesc d = c->desc(g_scale);
-  if (double *h = c->read_back(fld * (1 + c->D))) {
+  if (double *h = lbm::borrow_pinned(fld * (1 + c->D))) {
     HIP_TRY(c->ops->moments(d, h, h + c->N, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     if (rho) std::memcpy(rho, h, fld);
     if (u) std::memcpy(u, h + c->N, fld * c->D);
+    lbm::return_pinned(h);
     return poll_checks(c, true);
   }
   int rc = c->need_scratch(fld * (1 + c->D));
