@@ -193,6 +193,11 @@ inline int64_t monitor_blocks(const LaunchDesc &d) {
   const int64_t t = monitor_tiles(d);
   return t < MONITOR_BLOCKS ? t : MONITOR_BLOCKS;
 }
+// Records the blocks leave at most, whatever the block shape (64 x 1 makes the most tiles).
+inline int64_t monitor_records(int nx, int ny, int nz) {
+  const int64_t t = ((int64_t)nx + 63) / 64 * ny * nz;
+  return t < MONITOR_BLOCKS ? t : MONITOR_BLOCKS;
+}
 
 inline dim3 grid_of(const LaunchDesc &d) {
   return dim3((d.geo.nx + d.bx - 1) / d.bx, (d.geo.ny + d.by - 1) / d.by, d.geo.nz);

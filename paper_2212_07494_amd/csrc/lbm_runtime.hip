@@ -218,7 +218,7 @@ struct lbm_ctx {
   std::vector<uint32_t> smask_host;       // the same on the host (upload source, identity)
   void *uprev = nullptr;
   int64_t uprev_time = -2;
-  double *partials = nullptr;  // of the monitor pass (MONITOR_BLOCKS records)
+  double *partials = nullptr;  // of the monitor pass (monitor_records)
   double *mon_dev = nullptr;
   // In-step monitor checks (monitor_every > 0): the device record of time dev_step (-1:
   // none) and its mode; the latest check's copy in pinned host memory (mon_host) with the
@@ -895,7 +895,8 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
       (p->solid && (rc = c->dalloc((void **)&c->smask, (size_t)c->N * sizeof(uint32_t)))) ||
       (rc = c->dalloc(&c->uprev, 3 * (size_t)c->N * ab)) ||
       (rc = c->dalloc((void **)&c->partials,
-                      (size_t)lbm::MONITOR_BLOCKS * lbm::MON_SLOTS * sizeof(double))) ||
+                      (size_t)lbm::monitor_records(p->nx, p->ny, p->nz) * lbm::MON_SLOTS *
+                          sizeof(double))) ||
       (rc = c->dalloc((void **)&c->mon_dev, lbm::MON_SLOTS * sizeof(double)))) {
     std::string msg = g_last_error;
     release(c);
