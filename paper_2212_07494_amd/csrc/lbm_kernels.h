@@ -328,8 +328,8 @@ __device__ __forceinline__ void step_node(const S *__restrict__ fin, S *__restri
   }
 }
 
-// PLAIN: a lattice without walls or solid nodes whose rows fill wavefronts; the kernel then
-// holds neither linear blocks nor 32-bit offsets with bounce-back, which cost such lattices 1%
+// PLAIN: blocks of rows that do not gain by 32-bit offsets (rows_plain); the kernel then holds
+// neither linear blocks nor those offsets, which cost lattices without walls or solid nodes 1%
 // (D3Q27 FP32-shifted 128^3: 76.9 against 78.0 us a step, D3Q19 256^3 408 against 412).
 template <class L, int COLL, class S, class T, int GK, int MEM, bool PLAIN>
 __global__ void __launch_bounds__(256) step_kernel(StepArgs<T> a) {

@@ -81,12 +81,10 @@ struct Ops {
     a.small = (uint64_t)L::Q * d.geo.nz * d.geo.ps * sizeof(S) < (1ull << 32);
     const unsigned nb = (unsigned)(((int64_t)d.geo.nx * d.geo.ny + d.bx * d.by - 1) / (d.bx * d.by));
     const dim3 grid = d.linear ? dim3(nb, 1, d.geo.nz) : grid_of(d);
-    const bool plain = !d.linear && !d.geo.smask && !d.geo.wall[0] && !d.geo.wall[1] &&
-                       !d.geo.wall[2];
-    // (D2Q9 takes single steps for remainders only: one kernel serves both)
-    if (L::D == 3 && plain)
-      hipLaunchKernelGGL((step_kernel<L, COLL, S, T, GK, MEM, L::D == 3>), grid,
-                         dim3(d.bx, d.by), d.lds_pad, s, a);
+    const bool across_x = d.geo.wall[0] || d.geo.smask;
+    if (!d.linear && rows_plain(L::Q, sizeof(S), across_x, d.geo.wall[1] || d.geo.wall[2]))
+      hipLaunchKernelGGL((step_kernel<L, COLL, S, T, GK, MEM, true>), grid, dim3(d.bx, d.by),
+                         d.lds_pad, s, a);
     else
       hipLaunchKernelGGL((step_kernel<L, COLL, S, T, GK, MEM, false>), grid, dim3(d.bx, d.by),
                          d.lds_pad, s, a);

@@ -25,6 +25,19 @@ inline size_t workgroup_lds(int lds_cu, int lds_block) {
   return least > 0 ? (size_t)least : 0;
 }
 
+// Whether blocks of rows address through plane pointers where a pull may bounce back, rather
+// than through 32-bit offsets (step_kernel's PLAIN).  across_x: walls across x or solid nodes,
+// so that any block may bounce back; walls: walls across y or z, so that only blocks at them do.
+// The offsets pay in binary16, and on D3Q27 where every block needs them (us a step, pointers /
+// offsets: D3Q19 FP16-shifted 128^3 walls yz 34.8 / 31.1, D3Q27 FP64 128^3 walls xyz 168 / 162);
+// elsewhere they cost more than they save (D3Q19 FP32-shifted 128 x 64 x 64 walls xyz 14.2 /
+// 14.8, 256 x 128 x 128 walls y 102 / 105, D3Q27 FP64 96 x 96 x 128 walls y 90 / 91, D2Q9 FP64
+// 1024^2 23.6 / 24.4).
+inline bool rows_plain(int Q, size_t elem, bool across_x, bool walls) {
+  if (elem == 2) return !across_x && !walls;
+  return Q != 27 || !across_x;
+}
+
 // Several steps of a two-dimensional lattice in one launch (lbm_multistep.h): columns of a
 // tile, steps of a launch (and of one on the smallest lattices), threads of a workgroup, and
 // the most rows a plan lets a tile own.

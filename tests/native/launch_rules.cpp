@@ -22,6 +22,10 @@ int main() {
       const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem,
                                                lbm::workgroup_lds(cu, block), ncu);
       std::printf("%d %d %d %d %d %d %u\n", p.K, p.wx, p.ox, p.oy, p.ntx, p.nty, p.lds);
+    } else if (!std::strcmp(what, "rows_plain")) {  // Q bytes across_x walls
+      int Q, elem, across_x, walls;
+      if (std::scanf("%d %d %d %d", &Q, &elem, &across_x, &walls) != 4) return 1;
+      std::printf("%d\n", (int)lbm::rows_plain(Q, (size_t)elem, across_x != 0, walls != 0));
     } else if (!std::strcmp(what, "pieces")) {  // n size -> count, last start, last length
       long long n;
       int size, count = 0, start = 0, length = 0;

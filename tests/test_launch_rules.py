@@ -83,3 +83,12 @@ def test_tiles_fit_a_workgroup(ask, cu, block, most):
     """The LDS of a tile is what one workgroup may take, not what a compute unit has."""
     (K, *_, lds), = ask([("multi_plan", 1024, 1024, 0, 8, cu, block, NCU)])
     assert lds <= most and (K > 0) == (most > 0)
+
+
+def test_rows_plain(ask):
+    """Without walls and solid nodes always; with them, where the offsets cost more."""
+    for Q in (9, 19, 27, 39):
+        for elem in (2, 4, 8):
+            got = [v for v, in ask([("rows_plain", Q, elem, x, w) for x in (0, 1) for w in (0, 1)])]
+            assert got[0] == 1
+            assert got[1:] == ([0, 0, 0] if elem == 2 else [1, 0, 0] if Q == 27 else [1, 1, 1])
