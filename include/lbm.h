@@ -289,8 +289,8 @@ int lbm_save(lbm_ctx *c, const char *path);
 int lbm_load(lbm_ctx *c, const char *path);
 
 /* Launch configuration of the step kernel: block shape bx x by (bx in {64, 128, 256},
- * bx * by <= 256; 64 x 2, where nx is no multiple of 64, takes 128 consecutive nodes of a
- * layer instead of two rows) and variant 0..59, whose base b = variant % 12 selects the memory
+ * bx * by <= 256; 64 x 3, where nx is no multiple of 64, takes 128 consecutive nodes of a
+ * layer instead of three rows) and variant 0..59, whose base b = variant % 12 selects the memory
  * access b % 3 (0 plain loads and stores, 1 non-temporal stores, 2 non-temporal loads and
  * stores); (b / 3) odd also lets workgroups that cannot bounce back (no solid nodes, away
  * from wall faces) address each population plane through a scalar base and 32-bit

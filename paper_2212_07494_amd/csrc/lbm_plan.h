@@ -25,6 +25,17 @@ inline size_t workgroup_lds(int lds_cu, int lds_block) {
   return least > 0 ? (size_t)least : 0;
 }
 
+// Whether a step's blocks take consecutive nodes of a layer, 128 a block: on ragged widths, where
+// rows leave lanes idle, the block shape 64 x 3 stands for them (rows of 64 x 3 threads are no
+// faster than 64 x 2 or 64 x 4 anywhere); every other shape is rows.  The tuner measures both
+// kinds: D3Q27 of 72 columns FP32-shifted 27 us linear against 34 in rows, 150 columns FP64
+// 111 / 128 tuned, but tuned 120 columns FP16-shifted 31.1 / 28.3, 160 columns FP32-shifted
+// 61.7 / 58.6, and D2Q9 FP64 100000 x 2 9.4 / 6.4 (64 x 2: both rows in a block).
+constexpr int LINEAR_SHAPE = 3, LINEAR_BY = 2;  // 64 x 3 stands for 128 threads
+inline bool linear_blocks(int nx, int bx, int by) {
+  return nx % 64 != 0 && bx == 64 && by == LINEAR_SHAPE;
+}
+
 // Whether blocks of rows address through plane pointers where a pull may bounce back, rather
 // than through 32-bit offsets (step_kernel's PLAIN).  across_x: walls across x or solid nodes,
 // so that any block may bounce back; walls: walls across y or z, so that only blocks at them do.

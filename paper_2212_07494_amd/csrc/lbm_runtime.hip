@@ -149,17 +149,11 @@ int default_variant(size_t pop_bytes) { return 2 * pop_bytes <= kCachedBytes ? 9
 // Block shape: 256 threads of whole wavefronts along x, the widest rows among those that
 // leave the fewest lanes idle (192 columns: 64 x 4 rather than 128 x 2, D3Q27 FP64 516 against
 // 631 us a step, FP32-shifted 263 against 317, D3Q19 FP32-shifted 185 against 225); on ragged
-// widths 64 x 2, whose steps take consecutive nodes (linear_blocks).
+// widths consecutive nodes (linear_blocks).
 void block_shape(int nx, int &bx, int &by) {
   bx = nx % 128 ? 64 : nx % 256 ? 128 : 256;
-  by = nx % 64 ? 2 : 256 / bx;
+  by = nx % 64 ? lbm::LINEAR_SHAPE : 256 / bx;
 }
-
-// Whether a step's blocks take consecutive nodes: on ragged widths, where rows leave lanes
-// idle, blocks of 64 x 2; the other shapes stay rows.  The tuner measures both: D3Q27 of 72
-// columns FP32-shifted 27 us linear against 34 in rows, 150 columns FP64 111 / 128 tuned, but
-// tuned 120 columns FP16-shifted 31.1 / 28.3, 160 columns FP32-shifted 61.7 / 58.6.
-bool linear_blocks(int nx, int bx, int by) { return nx % 64 != 0 && bx == 64 && by == 2; }
 
 }  // namespace
 
@@ -342,8 +336,9 @@ struct lbm_ctx {
     // rows that fill no wavefront leave its last lanes idle, and as many memory requests
     // for them; consecutive nodes of the layer fill them all (D3Q19 BGK FP64 131 x 67 x 59
     // with walls: 39.7 -> 31.5 us a step as launched by default then, 160^3 FP64 267 -> 215)
-    d.linear = linear_blocks(p.nx, bx, by);
-    d.lds_pad = lds_for_cap(kWaveCaps[variant / kBaseVariants], bx, by, lds_cu, lds_block);
+    d.linear = lbm::linear_blocks(p.nx, bx, by);
+    if (d.linear) d.by = lbm::LINEAR_BY;
+    d.lds_pad = lds_for_cap(kWaveCaps[variant / kBaseVariants], d.bx, d.by, lds_cu, lds_block);
     return d;
   }
 };
@@ -1586,19 +1581,13 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
   HIP_TRY(hipEventCreate(&e1));
   const int cur0 = c->cur;
   int status = LBM_OK;
-  // one timed trial of a launch configuration; false on a device error (status set)
-  auto trial = [&](int bx, int by, int v) -> bool {
-    c->bx = bx;
-    c->by = by;
-    c->variant = v;
-    // warm-up launch, then the timed ones
-    lbm::LaunchDesc d = c->desc(1.0);
-    hipError_t e = c->ops->step(d, c->stream);
-    c->cur ^= 1;
-    if (e == hipSuccess) e = hipEventRecord(e0, c->stream);
-    for (int s = 0; s < steps && e == hipSuccess; ++s) {
-      d = c->desc(1.0);
-      e = c->ops->step(d, c->stream);
+  // ms a step of n steps as c is set up, after one more; < 0 on a device error (status set)
+  auto timed = [&](int n) -> float {
+    hipError_t e = hipSuccess;
+    for (int s = -1; s < n && e == hipSuccess; ++s) {
+      if (s == 0) e = hipEventRecord(e0, c->stream);
+      if (e != hipSuccess) break;
+      e = c->ops->step(c->desc(1.0), c->stream);
       c->cur ^= 1;
     }
     if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
@@ -1607,10 +1596,27 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
     if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
     if (e != hipSuccess) {
       status = fail(LBM_EDEVICE, "autotune trial failed: %s", hipGetErrorString(e));
-      return false;
+      return -1.0f;
     }
-    ms /= steps;
-    const int linear = linear_blocks(c->p.nx, bx, by);
+    return ms / n;
+  };
+  // one timed trial of a launch configuration; false on a device error.  One whose first
+  // quarter is 1.3 times as slow as the fastest so far ends there.
+  auto trial = [&](int bx, int by, int v) -> bool {
+    c->bx = bx;
+    c->by = by;
+    c->variant = v;
+    const int part = (steps + 3) / 4;
+    float ms = timed(part);
+    if (ms < 0) return false;
+    const float best = std::min(kind_ms[0] < 0 ? ms : kind_ms[0], kind_ms[1] < 0 ? ms : kind_ms[1]);
+    if (ms > 1.3f * best) return true;
+    if (steps > part) {
+      const float rest = timed(steps - part);
+      if (rest < 0) return false;
+      ms = (ms * part + rest * (steps - part)) / steps;
+    }
+    const int linear = lbm::linear_blocks(c->p.nx, bx, by);
     if (kind_ms[linear] < 0 || ms < kind_ms[linear]) {
       kind_ms[linear] = ms;
       kind[linear] = {bx, by, v};
@@ -1620,8 +1626,9 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
   // block shapes x base variants, every workgroup resident that the registers allow ...
   for (int bx : {64, 128, 256}) {
     if (bx > 64 && bx >= 2 * c->p.nx) continue;  // mostly idle lanes
-    for (int by : {1, 2, 4}) {
+    for (int by : {1, 2, lbm::LINEAR_SHAPE, 4}) {
       if (bx * by > 256) continue;
+      if (by == lbm::LINEAR_SHAPE && !lbm::linear_blocks(c->p.nx, bx, by)) continue;
       for (int v = 0; v < kBaseVariants && !status; ++v) trial(bx, by, v);
       if (status) break;
     }
