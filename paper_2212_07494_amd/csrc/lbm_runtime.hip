@@ -1601,7 +1601,7 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
     return ms / n;
   };
   // one timed trial of a launch configuration; false on a device error.  One whose first
-  // quarter is 1.3 times as slow as the fastest so far ends there.
+  // quarter is 1.1 times as slow as the fastest so far ends there.
   auto trial = [&](int bx, int by, int v) -> bool {
     c->bx = bx;
     c->by = by;
@@ -1610,7 +1610,7 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
     float ms = timed(part);
     if (ms < 0) return false;
     const float best = std::min(kind_ms[0] < 0 ? ms : kind_ms[0], kind_ms[1] < 0 ? ms : kind_ms[1]);
-    if (ms > 1.3f * best) return true;
+    if (ms > 1.1f * best) return true;
     if (steps > part) {
       const float rest = timed(steps - part);
       if (rest < 0) return false;
@@ -1638,8 +1638,11 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
   // best linear blocks, which gain differently: D3Q27 FP32-shifted of 150 columns 68.4 us
   // with the caps of the faster of the two alone, 62.7 with both)
   const lbm_tuning stage1[2] = {kind[0], kind[1]};
+  auto in_reach = [&](int i) {
+    return kind_ms[i] >= 0 && (kind_ms[i ^ 1] < 0 || kind_ms[i] < 1.2f * kind_ms[i ^ 1]);
+  };
   for (int i = 0; i < 2; ++i)
-    for (int k = 1; k < kNumCaps && kind_ms[i] >= 0 && !status; ++k)
+    for (int k = 1; k < kNumCaps && in_reach(i) && !status; ++k)
       if (lds_for_cap(kWaveCaps[k], stage1[i].bx, stage1[i].by, c->lds_cu, c->lds_block))
         trial(stage1[i].bx, stage1[i].by, stage1[i].variant % kBaseVariants + k * kBaseVariants);
   (void)hipEventDestroy(e0);
