@@ -36,6 +36,69 @@ inline bool linear_blocks(int nx, int bx, int by) {
   return nx % 64 != 0 && bx == 64 && by == LINEAR_SHAPE;
 }
 
+// Launch of the single step before any tuning: block shape and variant (0 plain; on the
+// scalar-base path 3 plain, 4 with non-temporal stores, 9 placed XCD by XCD).
+//
+// Blocks: rows of whole wavefronts, the widest among those that leave the fewest lanes idle (192
+// columns: 64 x 4 rather than 128 x 2, D3Q27 FP64 516 against 631 us a step); consecutive nodes
+// on ragged widths (D3Q27 FP64 300 x 100 x 100 222 against 383 us, 1000 x 64 x 64 300 / 352), but
+// where rows stay the better (D3Q19 FP16-shifted 4097 x 16 x 16 21.8 linear / 20.1, D3Q39
+// FP32-shifted 127^3 178 / 166, D2Q9 FP64 100000 x 2 9.4 / 6.4).  Few D2Q9 rows stand above one
+// another, so that a compute unit reads its neighbours' rows once (FP64 256^2 64 x 4 4.3 against
+// 256 x 1 5.6).
+// Variant, by the bytes of the two population buffers: beyond the 256 MB last-level cache
+// non-temporal stores (D3Q27 FP64 128^3 166 against 179 us; not where it is nearly full: D3Q19
+// FP32-shifted 128 x 128 x 256 plain 52.5 / 54.5).  Within it XCD placement pays for consecutive
+// nodes (D3Q19 FP32-shifted 100^3 26.3 against 32.1), on D2Q9 (FP64 1024^2 22.9 / 24.6) and for
+// rows (D3Q19 FP64 64^3 3%) but for those of a few MB (D2Q9 1000 x 1 3.2 / 2.9), of binary16
+// (D3Q19 128^3 36.1 / 28.3), of D3Q27 (FP32-shifted 64 x 64 x 128 1.004 / 0.938 of plain rows) or
+// with walls (D3Q19 FP32-shifted 64 x 128 x 64 walls y 14.8 / 14.1) well within the cache, and
+// with walls across x or solid nodes (D3Q19 FP32-shifted 128 x 128 x 96 5%).  There the
+// scalar-base path is the choice, which D3Q19 in FP32 does not earn (1-3% slower).
+struct StepLaunch {
+  int bx, by, variant;
+};
+inline StepLaunch default_launch(int Q, size_t elem, int nx, int ny, size_t bytes, bool across_x,
+                                 bool walls) {
+  constexpr size_t MIB = 1u << 20;
+  StepLaunch l{};
+  const int waves = ceil_div(nx, 64);
+  const int64_t idle = ceil_div(nx, 256) * int64_t(256) - nx;  // lanes of rows of 256
+  const bool rows = nx % 64 == 0 || (Q == 19 && elem == 2 && idle * 8 < nx) ||
+                    (Q == 39 && nx < 256 && nx % 64 >= 62) || (Q == 9 && ny <= 2);
+  if (!rows) {
+    l.bx = 64;
+    l.by = LINEAR_SHAPE;
+  } else if (Q == 9 && ny > 1 && bytes <= 32 * MIB) {
+    l.bx = 64;
+    l.by = ny < 4 ? 2 : 4;
+  } else {
+    l.bx = waves % 4 == 0 ? 256 : waves % 2 == 0 ? 128 : 64;
+    if (nx % 64 != 0 && nx > 256) l.bx = 256;
+    l.by = 256 / l.bx;
+  }
+  const bool f32_q19 = elem == 4 && Q != 27;
+  if (bytes > 320 * MIB)
+    l.variant = 4;
+  else if (bytes <= (Q == 9 ? 4 * MIB : MIB))
+    l.variant = 3;
+  else if (Q == 9)
+    l.variant = 9;
+  else if (elem == 2 && rows)
+    l.variant = 3;
+  else if (bytes > 256 * MIB)
+    l.variant = Q == 27 && rows ? 3 : 0;
+  else if (!rows)
+    l.variant = 9;
+  else if (across_x)
+    l.variant = f32_q19 ? 0 : 3;
+  else if (bytes > 144 * MIB || (Q != 27 && !walls))
+    l.variant = 9;
+  else
+    l.variant = f32_q19 ? 0 : 3;
+  return l;
+}
+
 // Whether blocks of rows address through plane pointers where a pull may bounce back, rather
 // than through 32-bit offsets (step_kernel's PLAIN).  across_x: walls across x or solid nodes,
 // so that any block may bounce back; walls: walls across y or z, so that only blocks at them do.

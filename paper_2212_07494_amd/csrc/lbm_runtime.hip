@@ -136,25 +136,6 @@ bool shifted(int s) { return s == LBM_F32_SHIFTED || s == LBM_F16_SHIFTED; }
 
 using lbm::ops_for;
 
-// Launch variant before any tuning, by the bytes of the two population buffers: while they
-// fit the 256 MB last-level cache, or nearly, plain accesses (the next step reads what this one
-// writes) and blocks placed XCD by XCD; beyond it non-temporal stores, in dispatch order.
-// Both on the scalar-base path.  Measured (us per step: general plain / 9 / 4): D3Q19
-// FP32-shifted 80^3 (78 MB) 17.0 / 15.3 / 18.5, 112^3 (214 MB) 39.0 / 37.5 / 41.3, 128^3
-// (319 MB) 60.7 / 54.7 / 58.0, 150^3 (513 MB) 110.8 / 107.0 / 105.5; D3Q27 FP64 84^3 (256 MB)
-// 53.2 / 45.3 / 50.8, 96^3 (382 MB) 83.0 / 78.3 / 72.6, 128^3 (1.8 GB) 171 / - / 166.
-constexpr size_t kCachedBytes = 320u << 20;
-int default_variant(size_t pop_bytes) { return 2 * pop_bytes <= kCachedBytes ? 9 : 4; }
-
-// Block shape: 256 threads of whole wavefronts along x, the widest rows among those that
-// leave the fewest lanes idle (192 columns: 64 x 4 rather than 128 x 2, D3Q27 FP64 516 against
-// 631 us a step, FP32-shifted 263 against 317, D3Q19 FP32-shifted 185 against 225); on ragged
-// widths consecutive nodes (linear_blocks).
-void block_shape(int nx, int &bx, int &by) {
-  bx = nx % 128 ? 64 : nx % 256 ? 128 : 256;
-  by = nx % 64 ? lbm::LINEAR_SHAPE : 256 / bx;
-}
-
 }  // namespace
 
 // Staging memory of lbm_get_populations_noalloc, which allocates nothing: node indices and
@@ -839,12 +820,19 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
         c->c4 = ((1.0 - 1.0 / p->tau_31) - (1.0 - 1.0 / p->tau[3])) / 2;
     }
   }
-  block_shape(p->nx, c->bx, c->by);
   if (c->ops->multi && !p->debug_poison)
     c->multi = lbm::multi_plan(p->nx, p->ny, p->bc[1] == LBM_WALLS, storage_bytes(p->storage),
                                lbm::workgroup_lds(c->lds_cu, c->lds_block), ncu);
   const size_t pop_bytes = (size_t)c->Q * (size_t)c->N * storage_bytes(p->storage);
-  c->variant = default_variant(pop_bytes);
+  {
+    const bool across_x = p->bc[0] == LBM_WALLS || p->solid;
+    const bool walls = p->bc[1] == LBM_WALLS || p->bc[2] == LBM_WALLS;
+    const lbm::StepLaunch l = lbm::default_launch(c->Q, storage_bytes(p->storage), p->nx, p->ny,
+                                                  2 * pop_bytes, across_x, walls);
+    c->bx = l.bx;
+    c->by = l.by;
+    c->variant = l.variant;
+  }
   const size_t ab = arith_bytes(p->storage);
   // force table, in the arithmetic type
   std::vector<double> gh;

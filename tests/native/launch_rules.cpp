@@ -22,6 +22,14 @@ int main() {
       const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem,
                                                lbm::workgroup_lds(cu, block), ncu);
       std::printf("%d %d %d %d %d %d %u\n", p.K, p.wx, p.ox, p.oy, p.ntx, p.nty, p.lds);
+    } else if (!std::strcmp(what, "default_launch")) {  // Q bytes nx ny buffers across_x walls
+      int Q, elem, nx, ny, across_x, walls;
+      long long bytes;
+      if (std::scanf("%d %d %d %d %lld %d %d", &Q, &elem, &nx, &ny, &bytes, &across_x, &walls) != 7)
+        return 1;
+      const lbm::StepLaunch l = lbm::default_launch(Q, (size_t)elem, nx, ny, (size_t)bytes,
+                                                    across_x != 0, walls != 0);
+      std::printf("%d %d %d %d\n", l.bx, l.by, l.variant, (int)lbm::linear_blocks(nx, l.bx, l.by));
     } else if (!std::strcmp(what, "rows_plain")) {  // Q bytes across_x walls
       int Q, elem, across_x, walls;
       if (std::scanf("%d %d %d %d", &Q, &elem, &across_x, &walls) != 4) return 1;

@@ -92,3 +92,34 @@ def test_rows_plain(ask):
             got = [v for v, in ask([("rows_plain", Q, elem, x, w) for x in (0, 1) for w in (0, 1)])]
             assert got[0] == 1
             assert got[1:] == ([0, 0, 0] if elem == 2 else [1, 0, 0] if Q == 27 else [1, 1, 1])
+
+
+def _default(ask, cases):
+    """(Q, bytes of a value, nx, ny, nz, walls across x, walls elsewhere)"""
+    return ask([("default_launch", Q, e, nx, ny, 2 * Q * e * nx * ny * nz, x, w)
+                for Q, e, nx, ny, nz, x, w in cases])
+
+
+def test_default_launch_is_valid(ask):
+    """A shape and variant that lbm_set_tuning takes; consecutive nodes on ragged widths only."""
+    cases = [(Q, e, nx, ny, nz, x, w) for Q in (9, 19, 27, 39) for e in (2, 4, 8)
+             for nx in (1, 3, 50, 64, 65, 126, 127, 128, 192, 256, 257, 1000, 4097, 65536, 2 ** 31 - 1)
+             for ny in (1, 2, 3, 40, 500) for nz in ((1,) if Q == 9 else (1, 60, 500))
+             for x in (0, 1) for w in (0, 1)]
+    for c, (bx, by, v, linear) in zip(cases, _default(ask, cases)):
+        assert bx in (64, 128, 256) and by >= 1 and bx * by <= 256 and 0 <= v < 12, c
+        assert linear == (by == 3) and not (linear and c[2] % 64 == 0), c
+
+
+@pytest.mark.parametrize("case,variants", [
+    # no XCD placement: binary16 rows, walls across x, walled FP32 rows well within the cache
+    ((19, 2, 128, 128, 128, 0, 0), (3,)), ((19, 2, 256, 128, 96, 1, 1), (3,)),
+    ((19, 4, 64, 128, 64, 1, 1), (0,)), ((19, 4, 64, 128, 64, 0, 1), (0,)),
+    ((27, 4, 64, 128, 64, 0, 0), (3,)), ((9, 8, 1000, 1, 1, 0, 0), (3,)),
+    # consecutive nodes, D2Q9 and periodic rows within the cache
+    ((19, 4, 100, 100, 100, 0, 0), (9,)), ((19, 8, 64, 64, 64, 0, 0), (9,)),
+    ((9, 8, 1024, 1024, 1, 0, 0), (9,)),
+    # non-temporal stores beyond it
+    ((27, 8, 128, 128, 128, 0, 0), (4,)), ((19, 4, 256, 256, 256, 0, 0), (4,))])
+def test_default_variant(ask, case, variants):
+    assert _default(ask, [case])[0][2] in variants
