@@ -342,6 +342,16 @@ int build_multi(lbm_batch *b) {
     rows = oy;
   }
   if (!rows) return LBM_OK;
+  int64_t n = 0, wave_rows = 0, blocks = 0;
+  for (const auto &m : b->dom) {
+    const int64_t cols = lbm::multi_columns(m.nx, K);
+    const int nty = lbm::ceil_div(m.ny, rows);
+    n += cols * nty;
+    wave_rows += cols * lbm::multi_rows(m.ny, lbm::ceil_div(m.ny, nty), K, m.wall[1]);
+    blocks += (m.N + 255LL) / 256;
+  }
+  if (!lbm::multi_pays(lbm::BATCH_RATES, sb, K, n, wave_rows, blocks, b->nodes, b->ncu))
+    return LBM_OK;
   std::vector<lbm::BatchMultiTile> tiles;
   int tallest = 0;
   try {

@@ -49,12 +49,13 @@ inline bool linear_blocks(int nx, int bx, int by) {
 // Variant, by the bytes of the two population buffers: beyond the 256 MB last-level cache
 // non-temporal stores (D3Q27 FP64 128^3 166 against 179 us; not where it is nearly full: D3Q19
 // FP32-shifted 128 x 128 x 256 plain 52.5 / 54.5).  Within it XCD placement pays for consecutive
-// nodes (D3Q19 FP32-shifted 100^3 26.3 against 32.1), on D2Q9 (FP64 1024^2 22.9 / 24.6) and for
-// rows (D3Q19 FP64 64^3 3%) but for those of a few MB (D2Q9 1000 x 1 3.2 / 2.9), of binary16
-// (D3Q19 128^3 36.1 / 28.3), of D3Q27 (FP32-shifted 64 x 64 x 128 1.004 / 0.938 of plain rows) or
-// with walls (D3Q19 FP32-shifted 64 x 128 x 64 walls y 14.8 / 14.1) well within the cache, and
-// with walls across x or solid nodes (D3Q19 FP32-shifted 128 x 128 x 96 5%).  There the
-// scalar-base path is the choice, which D3Q19 in FP32 does not earn (1-3% slower).
+// nodes (D3Q19 FP32-shifted 100^3 26.3 against 32.1), on D2Q9 of a few rows an XCD (FP64 1024^2
+// 22.9 / 24.6, but FP32-shifted 131072 x 4 10.1 / 7.7) and for rows (D3Q19 FP64 64^3 3%) but for
+// those of binary16 (D3Q19 128^3 36.1 / 28.3), of D3Q27 (FP32-shifted 64 x 64 x 128 1.004 /
+// 0.938 of plain rows) or with walls (D3Q19 FP32-shifted 64 x 128 x 64 walls y 14.8 / 14.1) well
+// within the cache, with walls across x or solid nodes (D3Q19 FP32-shifted 128 x 128 x 96 5%)
+// and the smallest (D2Q9 1000 x 1 3.2 / 2.9).  There the scalar-base path is the choice, which
+// D3Q19 in FP32 does not earn (1-3% slower).
 struct StepLaunch {
   int bx, by, variant;
 };
@@ -83,7 +84,7 @@ inline StepLaunch default_launch(int Q, size_t elem, int nx, int ny, size_t byte
   else if (bytes <= (Q == 9 ? 4 * MIB : MIB))
     l.variant = 3;
   else if (Q == 9)
-    l.variant = 9;
+    l.variant = ny >= 16 ? 9 : !rows || bytes <= 32 * MIB ? 3 : 0;
   else if (elem == 2 && rows)
     l.variant = 3;
   else if (bytes > 256 * MIB)
@@ -151,6 +152,51 @@ inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
   return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
 }
 
+// Rows (wavefronts of 64 lanes) that the K stages of one column of tiles compute: tiles of oy
+// rows down ny, each stage widened by up to K - 1 rows on both sides but not past a wall.
+inline int64_t multi_rows(int ny, int oy, int K, bool wy) {
+  const int64_t nty = ceil_div(ny, oy);
+  auto tile = [&](int64_t y0) {
+    const int64_t h = ny - y0 < oy ? ny - y0 : oy;
+    int64_t rows = 0;
+    for (int m = 0; m < K; ++m) {
+      const int64_t below = wy && y0 < m ? y0 : m;
+      const int64_t above = wy && ny - y0 - h < m ? ny - y0 - h : m;
+      rows += below + h + above;
+    }
+    return rows;
+  };
+  if (nty <= 4) {
+    int64_t rows = 0;
+    for (int64_t t = 0; t < nty; ++t) rows += tile(t * oy);
+    return rows;
+  }
+  return tile(0) + tile((nty - 1) * oy) + (nty - 2) * (K * (int64_t)oy + K * (K - 1));
+}
+
+// Whether launches of K steps are faster than single steps: a launch's tiles and their rows,
+// which the compute units take in turn, against the nodes of a single step and its workgroups
+// of 256 (which a batch's small domains leave mostly idle).  ns a tile, a row and a workgroup,
+// us a launch, ps a node, for binary16, FP32 and FP64; fitted to 4,450 lattices and 250
+// batches, where the choice is within 10% of the faster (us a step, single / several: 1 x 65535
+// FP64 4.3 / 39, 12 x 65535 FP32-shifted 11.6 / 20.5, 2097152 x 1 walls y 24 / 44, but 2048 x
+// 1024 24 / 13; 3000 domains of 3 x 200 FP64 41 / 384, of 16 x 16 18 / 38, but 732 of 64 x 64
+// 74 / 42).
+struct MultiRates {
+  double tile, row, launch, block, node;
+};
+constexpr MultiRates LATTICE_RATES[3] = {
+    {8.6, 0.48, 2.0, 0, 22}, {8.6, 0.48, 2.0, 0, 30}, {8.2, 0.75, 1.8, 0, 37}};
+constexpr MultiRates BATCH_RATES[3] = {
+    {9.4, 0.40, 4.0, 1.7, 8.2}, {9.4, 0.40, 4.0, 1.7, 8.2}, {12.5, 0.62, 2.8, 0.6, 25}};
+inline bool multi_pays(const MultiRates (&rates)[3], size_t elem, int K, int64_t tiles,
+                       int64_t rows, int64_t blocks, int64_t nodes, int ncu) {
+  const MultiRates &r = rates[elem == 2 ? 0 : elem == 4 ? 1 : 2];
+  const double turns = double((tiles + ncu - 1) / ncu) * ncu / double(tiles);
+  const double several = turns * (double(tiles) * r.tile + double(rows) * r.row) / K * 1e-3;
+  return several < r.launch + double(blocks) * r.block * 1e-3 + double(nodes) * r.node * 1e-6;
+}
+
 // Steps, columns and rows of the tiles.  A launch whose tiles each find a compute unit of
 // their own lasts as long as one tile, whose stages take their rows in passes of the
 // workgroup's wavefronts: about six rows' worth of latency a pass besides the rows themselves,
@@ -158,7 +204,7 @@ inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
 // the idle units pay for the wider margins (us a step, 64 against 32 columns: 64 x 32 BGK FP64
 // 1.80 / 1.58, 50 x 200 SMRT FP64 1.61 / 1.47, 128^2 FP64 1.57 / 1.46, 256^2 FP64 2.07 / 1.94);
 // and more steps a launch, where their rows still make one pass.  Launches with more tiles than
-// units are bound by the rows (multi_cost).
+// units are bound by the rows (multi_cost), if they pay at all (multi_pays).
 inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, size_t lds, int ncu) {
   MultiPlan p{};
   // a plane's byte offsets are 32-bit in the kernel
@@ -194,7 +240,12 @@ inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, size_t lds, in
     consider(few, MULTI_W, true);
     consider(few, 32, true);
     if (wy || ny >= 2 * MULTI_STEPS_MAX) consider(MULTI_STEPS_MAX, 32, true);
-    if (!p.K) consider(few, MULTI_W, false);
+    if (!p.K) {
+      consider(few, MULTI_W, false);
+      if (p.K && !multi_pays(LATTICE_RATES, elem, p.K, (int64_t)p.ntx * p.nty,
+                             p.ntx * multi_rows(ny, p.oy, p.K, wy), 0, (int64_t)nx * ny, ncu))
+        return MultiPlan{};
+    }
   }
   if (!p.K) return p;
   p.ox = ceil_div(nx, p.ntx);

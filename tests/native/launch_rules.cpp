@@ -22,6 +22,18 @@ int main() {
       const lbm::MultiPlan p = lbm::multi_plan(nx, ny, wy != 0, (size_t)elem,
                                                lbm::workgroup_lds(cu, block), ncu);
       std::printf("%d %d %d %d %d %d %u\n", p.K, p.wx, p.ox, p.oy, p.ntx, p.nty, p.lds);
+    } else if (!std::strcmp(what, "multi_rows")) {  // ny oy K wy
+      int ny, oy, K, wy;
+      if (std::scanf("%d %d %d %d", &ny, &oy, &K, &wy) != 4) return 1;
+      std::printf("%lld\n", (long long)lbm::multi_rows(ny, oy, K, wy != 0));
+    } else if (!std::strcmp(what, "batch_pays")) {  // bytes K tiles rows blocks nodes ncu
+      int elem, K, ncu;
+      long long tiles, rows, blocks, nodes;
+      if (std::scanf("%d %d %lld %lld %lld %lld %d", &elem, &K, &tiles, &rows, &blocks, &nodes,
+                     &ncu) != 7)
+        return 1;
+      std::printf("%d\n", (int)lbm::multi_pays(lbm::BATCH_RATES, (size_t)elem, K, tiles, rows,
+                                                blocks, nodes, ncu));
     } else if (!std::strcmp(what, "default_launch")) {  // Q bytes nx ny buffers across_x walls
       int Q, elem, nx, ny, across_x, walls;
       long long bytes;

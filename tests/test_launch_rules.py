@@ -123,3 +123,41 @@ def test_default_launch_is_valid(ask):
     ((27, 8, 128, 128, 128, 0, 0), (4,)), ((19, 4, 256, 256, 256, 0, 0), (4,))])
 def test_default_variant(ask, case, variants):
     assert _default(ask, [case])[0][2] in variants
+
+
+def test_multi_rows(ask):
+    """The rows that the stages compute, counted one by one (but for walls within a margin of a
+    tile between the first and the last)."""
+    cases = [(ny, oy, K, w) for ny in (1, 2, 5, 12, 27, 28, 60, 131) for oy in (1, 3, 7, 22, 27)
+             for K in (3, 5, 7) for w in (0, 1) if -(-ny // oy) <= 4 or (oy >= K - 1 and (ny - 1) % oy >= K - 2)]
+    want = []
+    for ny, oy, K, w in cases:
+        n = 0
+        for y0 in range(0, ny, oy):
+            y1 = min(y0 + oy, ny)
+            for m in range(K):
+                n += (min(ny, y1 + m) - max(0, y0 - m)) if w else y1 - y0 + 2 * m
+        want.append([n])
+    assert ask([("multi_rows", *c) for c in cases]) == want
+
+
+@pytest.mark.parametrize("lattice,several", [
+    ((64, 32, 1, 8), 1), ((50, 200, 1, 8), 1), ((32, 32, 0, 8), 1), ((1024, 1024, 0, 4), 1),
+    ((2048, 2048, 0, 4), 1), ((65536, 3, 1, 8), 1), ((1, 5, 1, 8), 1),
+    # low or narrow, where the tiles' rows leave lanes and wavefronts idle
+    ((1, 65535, 0, 8), 0), ((8, 16384, 1, 8), 0), ((12, 65535, 0, 4), 0),
+    ((2097152, 1, 1, 4), 0), ((1048576, 1, 1, 8), 0), ((524288, 1, 1, 4), 0)])
+def test_lattices_that_take_several_steps(ask, lattice, several):
+    (K, *_), = ask([("multi_plan", *lattice, LDS, LDS, NCU)])
+    assert (K > 0) == bool(several)
+
+
+# bytes, steps, tiles, rows of a launch, blocks of 256 nodes, nodes
+@pytest.mark.parametrize("batch,several", [
+    ((8, 5, 2196, 340380, 11712, 2998272), 1),    # 732 domains of 64 x 64
+    ((8, 5, 24000, 3480000, 9000, 1800000), 0),   # 3000 of 3 x 200
+    ((8, 5, 3000, 300000, 3000, 768000), 0),      # 3000 of 16 x 16
+    ((8, 3, 3000, 45000, 3000, 27000), 0),        # 3000 of 3 x 3
+    ((4, 5, 117, 11700, 117, 29952), 1)])         # 117 of 16 x 16
+def test_batches_that_take_several_steps(ask, batch, several):
+    assert ask([("batch_pays", *batch, NCU)]) == [[several]]
