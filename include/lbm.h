@@ -312,9 +312,10 @@ int lbm_get_tuning(const lbm_ctx *c, lbm_tuning *t);
 /* Time every block shape with the variants 0..11 for `steps` steps (>= 1), then the
  * fastest of those (of the rows and of the consecutive nodes) with each wave cap
  * (variant + 12 k, k = 1..4), and keep the fastest
- * of all.  The state is saved before and restored after, so the simulation is
- * unchanged.  best and
- * best_ms (time per step of the winner) may be NULL.  Synchronises the stream and
+ * of all.  D2Q9 launches of several steps are timed too, and left out from then on if single
+ * steps are faster; best is the fastest launch of a single step either way.  The state is
+ * saved before and restored after, so the simulation is unchanged.  best and
+ * best_ms (time per step of what lbm_step takes from then on) may be NULL.  Synchronises the stream and
  * temporarily needs one extra population buffer of device memory. */
 int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms);
 

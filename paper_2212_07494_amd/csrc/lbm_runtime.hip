@@ -237,6 +237,8 @@ struct lbm_ctx {
   double c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0, shift = 0;
   int bx = 64, by = 4, variant = 0;
   lbm::MultiPlan multi{};         // K = 0: every step is a launch of its own
+  bool multi_slower = false;      // so the tuner found: single steps then
+  int multi_steps() const { return multi_slower ? 0 : multi.K; }
   int lds_cu = 0, lds_block = 0;  // LDS bytes of a CU and the most one workgroup may take
   lbm_monitors mon{};
 
@@ -951,7 +953,7 @@ constexpr int64_t kGraphMaxNodes = 1 << 21;  // larger lattices are not launch-b
 // Steps of one captured graph: an even number of launches of multi.K steps where the
 // lattice has such launches.
 int graph_chunk(const lbm_ctx *c) {
-  const int two = 2 * c->multi.K;
+  const int two = 2 * c->multi_steps();
   return two ? (kGraphChunk + two - 1) / two * two : kGraphChunk;
 }
 
@@ -966,7 +968,7 @@ bool graph_steps(const lbm_ctx *c, int64_t n) {
 // (each launch moves the state to the other buffer, so the buffers alternate as they do
 // step by step), or 1.
 int next_steps(const lbm_ctx *c, int64_t n) {
-  int k = (int)std::min<int64_t>(c->multi.K, n);
+  int k = (int)std::min<int64_t>(c->multi_steps(), n);
   if (k % 2 == 0) --k;
   return k >= 3 ? k : 1;
 }
@@ -1569,13 +1571,15 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
   HIP_TRY(hipEventCreate(&e1));
   const int cur0 = c->cur;
   int status = LBM_OK;
-  // ms a step of n steps as c is set up, after one more; < 0 on a device error (status set)
-  auto timed = [&](int n) -> float {
+  // ms a step of n launches of k steps as c is set up, after one more; < 0 on a device error
+  // (status set)
+  auto timed = [&](int n, int k = 1) -> float {
     hipError_t e = hipSuccess;
     for (int s = -1; s < n && e == hipSuccess; ++s) {
       if (s == 0) e = hipEventRecord(e0, c->stream);
       if (e != hipSuccess) break;
-      e = c->ops->step(c->desc(1.0), c->stream);
+      lbm::LaunchDesc d = c->desc(1.0);
+      e = launch_steps(c, d, k, nullptr, c->stream);
       c->cur ^= 1;
     }
     if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
@@ -1586,7 +1590,7 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
       status = fail(LBM_EDEVICE, "autotune trial failed: %s", hipGetErrorString(e));
       return -1.0f;
     }
-    return ms / n;
+    return ms / (n * k);
   };
   // one timed trial of a launch configuration; false on a device error.  One whose first
   // quarter is 1.1 times as slow as the fastest so far ends there.
@@ -1633,6 +1637,9 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
     for (int k = 1; k < kNumCaps && in_reach(i) && !status; ++k)
       if (lds_for_cap(kWaveCaps[k], stage1[i].bx, stage1[i].by, c->lds_cu, c->lds_block))
         trial(stage1[i].bx, stage1[i].by, stage1[i].variant % kBaseVariants + k * kBaseVariants);
+  // and, where the lattice has them, launches of several steps
+  const int K = c->multi.K;
+  const float multi_ms = K && !status ? timed((steps + K - 1) / K, K) : -1.0f;
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   // restore the state into the buffer it came from
@@ -1649,8 +1656,9 @@ int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms) {
   const float win_ms = kind_ms[lin];
   rc = lbm_set_tuning(c, &win);
   if (rc) return rc;
+  if (K) c->multi_slower = win_ms < multi_ms;
   if (best) *best = win;
-  if (best_ms) *best_ms = win_ms;
+  if (best_ms) *best_ms = K ? std::min(win_ms, multi_ms) : win_ms;
   return LBM_OK;
 }
 
