@@ -122,7 +122,10 @@ int lbm_batch_set_tuning(lbm_batch *b, const lbm_batch_tuning *t);
 int lbm_batch_get_tuning(const lbm_batch *b, lbm_batch_tuning *t);
 
 /* Time every launch configuration for `steps` steps on a saved copy of the state and
- * keep the fastest (the state is restored).  best / best_ms (per step) may be NULL. */
+ * keep the fastest (the state is restored).  D2Q9 launches of several steps are timed too,
+ * and left out from then on if single steps are faster; best is the fastest launch of a
+ * single step either way.  best and best_ms (time per step of what a step takes from then
+ * on) may be NULL. */
 int lbm_batch_autotune(lbm_batch *b, int32_t steps, lbm_batch_tuning *best, double *best_ms);
 
 /* Total nodes, tiles and device bytes of the batch (any pointer may be NULL). */
