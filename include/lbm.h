@@ -160,9 +160,9 @@ typedef struct {
    * 1/3) makes the call that reads it return the warning LBM_WMACH (the low-Mach
    * expansion behind the truncated equilibrium loses accuracy there).  0 = off. */
   double mach_limit;
-  /* Debug pass: 1 = before every step, fill the buffer the step writes with NaN, so a
-   * value that the next step pulls but this step did not write shows up as NaN in the
-   * results (every slot a step pulls is written by the step before it).  0 = off. */
+  /* Debug pass: 1 = before every launch (of one step or several), fill the buffer it writes
+   * with NaN, so a value that the next launch pulls but this one did not write shows up as
+   * NaN in the results (every slot a step pulls is written by the step before it).  0 = off. */
   int32_t debug_poison;
 } lbm_params;
 
@@ -196,9 +196,10 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init,
 
 /* Advance n >= 0 steps.  g_scale: NULL (s(t) = 1) or n host doubles, the factor s(t)
  * of g(x) for each step.  Enqueues work only (no synchronisation), except as below.
- * D2Q9: up to five steps (seven on small lattices) are taken by one launch (tiles that recompute their margins), except
- * with debug_poison or where a periodic lattice has fewer than three rows; the launch
- * configuration (lbm_tuning) is that of the single steps that remain.
+ * D2Q9: up to five steps (seven on small lattices) are taken by one launch (tiles that
+ * recompute their margins), except where a periodic lattice has fewer than three rows or
+ * single steps are faster (narrow or very low lattices, or so lbm_autotune found); the
+ * launch configuration (lbm_tuning) is that of the single steps that remain.
  * Small lattices (N <= 2^21 nodes), where launch overhead dominates: when n covers at
  * least two chunks of 64 steps (70 with five or seven steps a launch, 66 with three) and neither
  * monitor_every nor debug_poison is set, the chunks are replayed from a HIP graph captured

@@ -822,7 +822,7 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init, 
         c->c4 = ((1.0 - 1.0 / p->tau_31) - (1.0 - 1.0 / p->tau[3])) / 2;
     }
   }
-  if (c->ops->multi && !p->debug_poison)
+  if (c->ops->multi)
     c->multi = lbm::multi_plan(p->nx, p->ny, p->bc[1] == LBM_WALLS, storage_bytes(p->storage),
                                lbm::workgroup_lds(c->lds_cu, c->lds_block), ncu);
   const size_t pop_bytes = (size_t)c->Q * (size_t)c->N * storage_bytes(p->storage);
