@@ -507,7 +507,7 @@ def make_domain(shape, walls=(0, 0, 0), tau=(0.8, 0.8, 1.0), g=None, g_profile=N
 
 
 class Batch:
-    """Owns one lbm_batch context: many domains stepped by one persistent launch."""
+    """Owns one lbm_batch context: many domains stepped together."""
 
     def __init__(self, domains, lattice="D2Q9", collision="smrt", storage="f32s", rho0=1.0,
                  stream=None):
