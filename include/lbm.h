@@ -201,12 +201,12 @@ int lbm_init(const lbm_params *p, const double *rho_init, const double *u_init,
  * single steps are faster (narrow or very low lattices, or so lbm_autotune found); the
  * launch configuration (lbm_tuning) is that of the single steps that remain.
  * Small lattices (N <= 2^21 nodes), where launch overhead dominates: when n covers at
- * least two chunks of 64 steps (70 with five or seven steps a launch, 66 with three) and neither
- * monitor_every nor debug_poison is set, the chunks are replayed from a HIP graph captured
- * once per buffer parity (the factors s(t)
- * are then staged in pinned host memory, uploaded asynchronously and read on the device;
- * the call waits only for the previous call's upload to have completed); the remainder
- * runs as direct launches.  The results are identical to single launches of one step.
+ * least two chunks of 64 steps (70 with five or seven steps a launch, 66 with three) and
+ * neither monitor_every nor debug_poison is set, the chunks are replayed from a HIP graph
+ * captured once per buffer parity (the factors s(t) are then staged in pinned host memory,
+ * uploaded asynchronously and read on the device; the call waits only for the previous
+ * call's upload to have completed); the remainder runs as direct launches.  The results
+ * are identical to single launches of one step.
  * Monitors in the step: if monitor_every is K > 0, after every step whose time t is a
  * multiple of K the monitor record of time t is computed on the device (with the
  * residual against time t - 1, whose velocity is recorded one step earlier; K = 1
@@ -316,8 +316,8 @@ int lbm_get_tuning(const lbm_ctx *c, lbm_tuning *t);
  * of all.  D2Q9 launches of several steps are timed too, and left out from then on if single
  * steps are faster; best is the fastest launch of a single step either way.  The state is
  * saved before and restored after, so the simulation is unchanged.  best and
- * best_ms (time per step of what lbm_step takes from then on) may be NULL.  Synchronises the stream and
- * temporarily needs one extra population buffer of device memory. */
+ * best_ms (time per step of what lbm_step takes from then on) may be NULL.  Synchronises
+ * the stream and temporarily needs one extra population buffer of device memory. */
 int lbm_autotune(lbm_ctx *c, int32_t steps, lbm_tuning *best, double *best_ms);
 
 /* Stream-copy probe: dst = src for `bytes` bytes (multiple of 16) of device memory,

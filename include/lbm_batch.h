@@ -5,13 +5,14 @@
  * lbm.h (Li, Duan & Shan, arXiv 2212.07494, Sec. II.A eq:dv; the step is eq:evolution
  * with the BGK update eq:explict_eq or the SMRT update of Sec. II.C): its own size,
  * walls, relaxation times and acceleration field.  All domains share one lattice,
- * collision model and storage mode, and all are advanced by ONE persistent kernel
- * launch per time step: a fixed grid of workgroups walks a flattened table of
- * equal-sized tiles (one tile = one workgroup's worth of nodes of one domain), so
- * uneven domains load-balance.  On D2Q9 a launch takes up to five steps where every periodic
- * domain has at least three rows (one workgroup a tile, margins recomputed).  lbm_batch_run captures K steps plus the convergence
- * monitors as one HIP graph and replays it; per-domain convergence is decided on the
- * device, and the tiles of converged domains are skipped.
+ * collision model and storage mode, and all are advanced by ONE kernel launch per time
+ * step over a flattened table of equal-sized tiles (one tile = one workgroup's worth of
+ * nodes of one domain), so uneven domains load-balance: one workgroup a tile, or a fixed
+ * grid of workgroups that walk the table (lbm_batch_tuning).  On D2Q9 a launch takes up to
+ * five steps (one workgroup a tile, margins recomputed) where that is faster and every
+ * periodic domain has at least three rows.  lbm_batch_run captures K steps plus the
+ * convergence monitors as one HIP graph and replays it; per-domain convergence is decided
+ * on the device, and the tiles of converged domains are skipped.
  *
  * Conventions are those of lbm.h: status codes, lbm_last_error(), node order
  * n = (z ny + y) nx + x within a domain, population order, host arrays copied during

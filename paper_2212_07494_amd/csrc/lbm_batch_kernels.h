@@ -1,16 +1,16 @@
-// Kernels of the batched engine: many independent domains, one persistent launch per
-// step.
+// Kernels of the batched engine: many independent domains, one launch per step (D2Q9: up to
+// five steps a launch, batch_multi_kernel of lbm_d2q9_multi.h).
 //
 // Layout: the domains' populations are packed one domain after another in each of the
 // two population buffers (domain d occupies Q N_d values starting at element base_d, in
-// the single-lattice layout of pop_slot); velocities recorded for the residual are packed the same way (D
-// planes per domain); force tables / fields are packed into one table buffer.
+// the single-lattice layout of pop_slot); velocities recorded for the residual are packed
+// the same way (D planes per domain); force tables / fields are packed into one table buffer.
 //
 // Work decomposition: a flattened table of tiles, each tile = one 256-thread workgroup
-// of one domain (tbx x tby nodes of one z slice, tbx = 64, 128 or 256).  A fixed grid of
-// workgroups (a few per compute unit) walks the table with a stride of the grid size,
-// so domains of any size share the machine evenly; tiles of inactive (converged)
-// domains are skipped after reading one flag.
+// of one domain (256 consecutive nodes of one z slice, or tbx x tby nodes of it with tbx = 64,
+// 128 or 256).  One workgroup takes one tile, or a fixed grid of workgroups (a few per compute
+// unit) walks the table with a stride of the grid size (a launch choice); tiles of inactive
+// (converged) domains are skipped after reading one flag.
 #pragma once
 
 #include "lbm_kernels.h"

@@ -477,7 +477,7 @@ __global__ void __launch_bounds__(256) scatter_kernel(S *__restrict__ f, Geom ge
 // the rows, so an amplitude is read once per row group); then the nodes' sums, B by
 // broadcast.  With one sincos and 4 Q operations a wave and node (the sum as written) the
 // 128^3 D3Q27 start of 185 waves (9 groups) took 4.04 ms, bound by the binary64 ALU; grouped
-// 0.33 ms, of which writing the populations needs 0.07.  208 VGPRs leave two workgroups a
+// 0.34 ms, of which writing the populations needs 0.07.  208 VGPRs leave two workgroups a
 // compute unit, whose phases overlap little, so latency is what remains: eight amplitudes and
 // eight B in flight together (0.52 -> 0.47 ms), most waves in one pass (WV_SUB 64: 0.45, 128:
 // 0.39).

@@ -32,16 +32,19 @@
 // twice the bare arithmetic of the widened tile's nodes.  With one or two wavefronts a SIMD,
 // as on the smallest lattices, an instruction takes about eight cycles instead of four, and a
 // stage's chain of them (1,400 to 2,500 cycles) is the floor.  Measured, us per step, single
-// steps against these launches: 64 x 32 BGK FP64 3.1 / 1.55; 50 x 200 SMRT FP64 3.2 / 1.45;
-// 512^2 FP64 9.4 / 4.3; 1024^2 SMRT FP32-shifted 13.4 / 8.1, FP64 24.9 / 13.6; 2048^2
-// FP32-shifted 57 / 26; a batch of 512 domains (5.8 million nodes) FP32-shifted 120 / 52.
+// steps against these launches as planned (SMRT but for the first, in one run): 64 x 32 BGK
+// FP64 3.0 / 1.57; 50 x 200 FP64 3.0 / 1.45; 512^2 FP64 10.0 / 4.3; 1024^2 FP32-shifted 13.8 /
+// 7.9, FP64 25.3 / 14.0; 2048^2 FP32-shifted 57 / 26; a batch of 512 domains (5.8 million
+// nodes) FP32-shifted 120 / 49.  A launch of that batch reads its populations once (0.21 GB) and
+// writes 1.8 times them (0.38 GB, by the counters).
 //
-// Why five.  Three and seven steps a launch of 64-column tiles were slower at every size tried
-// (128^2: 1.57 and 1.95 against 1.37; 900^2 FP32-shifted: 6.2 and 8.2 against 6.1): fewer leave
-// more of the launch, more widen the tile.  Seven pay on 32-column tiles while their rows
-// make one pass of the wavefronts (32^2 FP64 1.27 against 1.35).  512 threads: more wavefronts
-// than a stage has rows idle, and two workgroups of eight wavefronts hide each other's
-// barriers (1024 threads: 10.3 against 8.1 at 1024^2).
+// Why five.  Fewer leave more of the launch, more widen the tile; three, five and seven steps
+// on 64-column tiles, us per step: 128^2 FP64 1.76 / 1.60 / 1.69, 512^2 FP32-shifted 3.10 / 2.91 /
+// 2.80, 900^2 6.5 / 6.8 / 6.9, 1024^2 8.8 / 8.0 / 9.4, FP64 15.1 / 13.8 / 15.5, 2048^2
+// FP32-shifted 30 / 26 / 37.  Seven pay on 32-column tiles while their rows make one pass of the
+// wavefronts (32^2 FP64 1.27 against 1.35).  512 threads: more wavefronts than a stage has rows
+// idle, and two workgroups of eight wavefronts hide each other's barriers (1024 threads: 10.3
+// against 8.1 at 1024^2).
 #pragma once
 
 #include <hip/hip_runtime.h>

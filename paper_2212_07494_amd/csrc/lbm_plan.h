@@ -145,9 +145,9 @@ inline int multi_steps(int ny, bool wy) { return wy || ny >= 12 ? MULTI_STEPS : 
 // Relative time of a launch of `tiles` tiles of oy rows: the compute units take them in
 // turn, and a tile costs the rows of its K stages and about five more for its start and end.
 // The fastest heights sit where the tiles just fill the compute units once, twice, ...:
-// 512^2 FP32-shifted (10 columns) 22 rows, 240 tiles, 2.95 us a step against 4.08 at 20 rows,
-// 260 tiles; 900^2 (17 columns) 20 rows, 765 tiles, 6.1 against 7.1 at 18 rows.  MULTI_ROWS
-// keeps two workgroups a compute unit in FP32 (28 rows at 2048^2: 36 us a step, 26: 26).
+// 512^2 FP32-shifted (10 columns) 22 rows, 240 tiles, 3.1 us a step against 4.4 at 20 rows,
+// 260 tiles; 900^2 (17 columns) 20 rows, 765 tiles, 7.0 against 8.0 at 18 rows.  MULTI_ROWS
+// keeps two workgroups a compute unit in FP32 (28 rows at 2048^2: 36 us a step, 27: 26).
 inline double multi_cost(int64_t tiles, int oy, int K, int ncu) {
   return double((tiles + ncu - 1) / ncu) * (K * oy + K * (K - 1) + 5);
 }
@@ -201,10 +201,11 @@ inline bool multi_pays(const MultiRates (&rates)[3], size_t elem, int K, int64_t
 // their own lasts as long as one tile, whose stages take their rows in passes of the
 // workgroup's wavefronts: about six rows' worth of latency a pass besides the rows themselves,
 // after 22 for the launch.  There rows of 32 columns, two to a wavefront, halve the passes, and
-// the idle units pay for the wider margins (us a step, 64 against 32 columns: 64 x 32 BGK FP64
-// 1.80 / 1.58, 50 x 200 SMRT FP64 1.61 / 1.47, 128^2 FP64 1.57 / 1.46, 256^2 FP64 2.07 / 1.94);
-// and more steps a launch, where their rows still make one pass.  Launches with more tiles than
-// units are bound by the rows (multi_cost), if they pay at all (multi_pays).
+// the idle units pay for the wider margins (us a step, five steps on 64 columns, on 32, seven
+// on 32: 64 x 32 BGK FP64 1.83 / 1.62 / 1.57, 50 x 200 SMRT FP64 1.63 / 1.50 / 1.46, 128^2 FP64
+// 1.60 / 1.49 / 1.42, 256^2 FP64 2.09 / 1.94 / 2.00); and more steps a launch, where their rows
+// still make one pass.  Launches with more tiles than units are bound by the rows (multi_cost),
+// if they pay at all (multi_pays).
 inline MultiPlan multi_plan(int nx, int ny, bool wy, size_t elem, size_t lds, int ncu) {
   MultiPlan p{};
   // a plane's byte offsets are 32-bit in the kernel
